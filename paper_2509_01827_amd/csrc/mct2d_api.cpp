@@ -29,6 +29,7 @@ using mct::StepParams;
 namespace {
 
 constexpr int kGraphSteps = 64;  // steps per captured graph segment
+constexpr int64_t kResidentMinSteps = 4;  // shorter requests take the per-step kernels
 constexpr int kNumOrders = 3;    // work-unit orders of a batch (see build_units)
 
 struct TractionEdge {
@@ -137,6 +138,10 @@ struct mct_ctx {
     hipGraphExec_t tgraph[2] = {nullptr, nullptr};
     int tgraph_tile[2] = {0, 0}, tgraph_n[2] = {0, 0};
     int64_t steps_enqueued = 0;  // host view of the step counter
+    // resident step of a plain grid: its plan (threads 0: not used) and the
+    // epochs its launches have taken
+    mct::ResidentPlan res{};
+    uint32_t res_epoch = 0;
 
     // state queries
     bool ev_alloc = false;
@@ -270,9 +275,17 @@ void free_screen(mct_ctx *c) {
     c->screen_on = false;
 }
 
+void free_resident(mct_ctx *c) {
+    dfree(c->res.xb);
+    dfree(c->res.slots);
+    c->res = mct::ResidentPlan{};  // err lies beside the control block
+    c->res_epoch = 0;
+}
+
 void release_device(mct_ctx *c) {
     if (c->stream) (void)hipStreamSynchronize(c->stream);
     drop_graphs(c);
+    free_resident(c);
     dfree(c->dX);
     dfree(c->dY);
     if (c->bound) {  // the caller's arrays
@@ -406,6 +419,7 @@ std::vector<int2> build_units(const mct_ctx *c, int order) {
 }
 
 void refresh_f32(mct_ctx *c);
+int plan_resident(mct_ctx *c);
 
 // (Re)build tile geometry, slot sets, views and work units for the chosen
 // tile shape and order.  Device state is untouched.
@@ -438,6 +452,27 @@ int set_launch_geometry(mct_ctx *c) {
         HIP_TRY(c, hipMalloc((void **)&c->dunits, sizeof(int2) * units.size()));
         HIP_TRY(c, hipMemcpy(c->dunits, units.data(), sizeof(int2) * units.size(), hipMemcpyHostToDevice));
     }
+    return plan_resident(c);
+}
+
+// The resident step runs the automatic launch choice of a plain grid that
+// fits on the chip, with the global pick; a chosen tile shape, single-tip
+// tracking, the per-front pick and the near-threshold log keep the per-step
+// kernels (as do requests without graphs, which a caller may capture).
+int plan_resident(mct_ctx *c) {
+    free_resident(c);
+    const StepParams &p = c->specs[0].prm;
+    if (c->batch || c->tile_req != 0 || p.sct || p.front || p.near) return MCT_OK;
+    mct::ResidentPlan r;
+    if (!mct::resident_plan(p.nx, p.ny, c->precision == 32, p.subcell != 0, c->device, r)) return MCT_OK;
+    HIP_TRY(c, hipMalloc((void **)&c->res.xb, sizeof(uint64_t) * r.words_u));
+    HIP_TRY(c, hipMalloc((void **)&c->res.slots, sizeof(uint64_t) * r.words_s));
+    r.xb = c->res.xb;
+    r.slots = c->res.slots;
+    r.err = reinterpret_cast<uint32_t *>(c->dctl + 1);
+    HIP_TRY(c, hipMemsetAsync(r.xb, 0, sizeof(uint64_t) * r.words_u, c->stream));
+    HIP_TRY(c, hipMemsetAsync(r.slots, 0, sizeof(uint64_t) * r.words_s, c->stream));
+    c->res = r;
     return MCT_OK;
 }
 
@@ -891,9 +926,19 @@ int upload(mct_ctx *c, T *&dst, const std::vector<T> &src) {
     return MCT_OK;
 }
 
+// The control block of specimen s; with the resident step also its error
+// word, which lies behind the block.
 int read_control(mct_ctx *c, int s, Control *h) {
-    HIP_TRY(c, hipMemcpyAsync(h, c->dctl + s, sizeof(Control), hipMemcpyDeviceToHost, c->stream));
+    struct {
+        Control ctl;
+        uint32_t err[4];
+    } v;
+    const bool res = c->res.threads != 0;
+    HIP_TRY(c, hipMemcpyAsync(&v, c->dctl + s, res ? sizeof v : sizeof(Control), hipMemcpyDeviceToHost, c->stream));
     HIP_TRY(c, hipStreamSynchronize(c->stream));
+    *h = v.ctl;
+    if (res && v.err[0])
+        return fail(c, MCT_EDEVICE, "resident step: a workgroup did not answer (step %lld)", (long long)v.ctl.base);
     return MCT_OK;
 }
 
@@ -1416,7 +1461,9 @@ int mct_finalize(mct_ctx *c) {
         }
         HIP_TRY(c, hipStreamSynchronize(c->stream));  // before the host vectors go
     }
-    HIP_TRY(c, hipMalloc((void **)&c->dctl, sizeof(Control) * c->specs.size()));
+    // (behind the blocks: the resident step's error word)
+    HIP_TRY(c, hipMalloc((void **)&c->dctl, sizeof(Control) * c->specs.size() + 16));
+    HIP_TRY(c, hipMemsetAsync(c->dctl + c->specs.size(), 0, 16, c->stream));
     {
         std::vector<Control> h0(c->specs.size());
         std::memset(h0.data(), 0, sizeof(Control) * h0.size());
@@ -1590,6 +1637,19 @@ int mct_step(mct_ctx *c, int64_t n) {
     if (n < 0) return fail(c, MCT_EINVAL, "negative step count");
     if (c->screen_on) return step_screened(c, n);
     int64_t left = n;
+    hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
+    if (c->use_graph && c->res.threads && n >= kResidentMinSteps &&
+        hipStreamIsCapturing(c->stream, &cap) == hipSuccess && cap == hipStreamCaptureStatusNone) {
+        while (left > 0) {
+            const int m = (int)std::min<int64_t>(left, mct::kResidentMaxSteps);
+            HIP_TRY(c, mct::launch_resident(c->res, launch_of(c), m, (int)(c->steps_enqueued & 1), c->res_epoch,
+                                            c->stream));
+            c->res_epoch += (uint32_t)m;
+            c->steps_enqueued += m;
+            left -= m;
+        }
+        return MCT_OK;
+    }
     if (c->use_graph) {
         while (left >= kGraphSteps) {
             const int par0 = (int)(c->steps_enqueued & 1);
@@ -1692,6 +1752,10 @@ int mct_sync(mct_ctx *c) {
         HIP_TRY(c, mct::launch_check_finite(c->dux[par], c->duy[par], c->dvx, c->dvy, nn, c->dflag, c->stream));
         HIP_TRY(c, hipMemcpyAsync(&flag, c->dflag, sizeof flag, hipMemcpyDeviceToHost, c->stream));
         HIP_TRY(c, hipStreamSynchronize(c->stream));
+        if (c->res.threads) {
+            Control h;
+            if ((rc = read_control(c, 0, &h))) return rc;
+        }
         if (flag) return fail(c, MCT_ENUMERIC, "non-finite displacement or velocity after step %lld",
                               (long long)c->steps_enqueued);
         return MCT_OK;
@@ -2170,7 +2234,7 @@ static int autotune_unstructured(mct_ctx *c, int trial_steps, int *tile_out, int
     if ((rc = mct::tri::restore(m, h, ck.data(), bytes))) return rc;
     if (tile_out) *tile_out = tri_launch_index(m);
     if (order_out) *order_out = 0;
-    if (us_per_step_out) *us_per_step_out = 1e3 * (double)best / trial_steps;
+    if (us_per_step_out) *us_per_step_out = 1e3 * (double)best;
     return MCT_OK;
 }
 
@@ -2186,25 +2250,31 @@ int mct_autotune(mct_ctx *c, int trial_steps, int *tile_out, int *order_out, dou
     if ((rc = mct_checkpoint(c, ck.data(), bytes, &bytes))) return rc;
     const int saved_tile = c->tile_req, saved_order = c->order_req;
     const bool saved_graph = c->use_graph;
-    c->use_graph = false;  // candidates are timed with direct launches
-    float best = INFINITY;
+    float best = INFINITY;  // per step
     int best_tile = 0, best_order = 0;
     const int norders = c->batch ? kNumOrders : 1;
     hipEvent_t e0 = nullptr, e1 = nullptr;
     if (hipEventCreate(&e0) != hipSuccess || hipEventCreate(&e1) != hipSuccess) rc = MCT_EDEVICE;
-    for (int t = 1; t <= mct::kNumTiles && rc == MCT_OK; ++t)
+    // choice 0 is the resident step, where the automatic choice runs it; the
+    // tile shapes are timed with direct launches
+    for (int t = 0; t <= mct::kNumTiles && rc == MCT_OK; ++t)
         for (int o = 0; o < norders && rc == MCT_OK; ++o) {
+            if (t == 0 && (c->batch || !saved_graph || c->screen_on)) continue;
+            c->use_graph = t == 0;
             c->tile_req = t;
             c->order_req = o;
             if ((rc = set_launch_geometry(c))) break;
+            if (t == 0 && !c->res.threads) continue;
+            const int trial = t == 0 ? std::max(trial_steps, 64) : trial_steps;
             if ((rc = mct_restore(c, ck.data(), bytes))) break;
-            if ((rc = mct_step(c, 2))) break;  // warm
+            if ((rc = mct_step(c, t == 0 ? kResidentMinSteps : 2))) break;  // warm
             if (hipEventRecord(e0, c->stream) != hipSuccess) rc = MCT_EDEVICE;
-            if (!rc) rc = mct_step(c, trial_steps);
+            if (!rc) rc = mct_step(c, trial);
             if (!rc && hipEventRecord(e1, c->stream) != hipSuccess) rc = MCT_EDEVICE;
             if (!rc && hipEventSynchronize(e1) != hipSuccess) rc = MCT_EDEVICE;
             float ms = 0.f;
             if (!rc && hipEventElapsedTime(&ms, e0, e1) != hipSuccess) rc = MCT_EDEVICE;
+            ms /= (float)trial;
             if (!rc && ms < best) {
                 best = ms;
                 best_tile = t;
@@ -2225,9 +2295,9 @@ int mct_autotune(mct_ctx *c, int trial_steps, int *tile_out, int *order_out, dou
     c->order_req = best_order;
     if ((rc = set_launch_geometry(c))) return rc;
     if ((rc = mct_restore(c, ck.data(), bytes))) return rc;
-    if (tile_out) *tile_out = best_tile;
+    if (tile_out) *tile_out = c->tile;
     if (order_out) *order_out = best_order;
-    if (us_per_step_out) *us_per_step_out = 1e3 * (double)best / trial_steps;
+    if (us_per_step_out) *us_per_step_out = 1e3 * (double)best;
     return MCT_OK;
 }
 

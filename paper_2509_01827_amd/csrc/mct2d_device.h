@@ -255,6 +255,62 @@ __device__ __forceinline__ void path_geom(const T x[4], const T y[4], int a, int
     path_geom_pts(x[a], y[a], x[a1], y[a1], x[k], y[k], x[k1], y[k1], nxo, nyo, len);
 }
 
+// Pieces of a split Q4 element, its nodes in order from the edge F the piece
+// starts at: node 0 and node 1 are F's ends, the piece runs counter-clockwise
+// from F's midpoint.  f: force on nodes 0..3 (x, y).
+//
+// Corner split: the three-node piece (nodes 1, 2, 3), a constant-strain
+// triangle carrying the area of the polygon mid(F), 1, 2, 3, mid(edge 3-0);
+// the one-node piece (node 0) has no stiffness.
+template <class T>
+__device__ __forceinline__ void corner_piece(const StepParamsT<T> &p, const T x[4], const T y[4], const T u[4],
+                                             const T v[4], T f[8]) {
+    const T gx = T(0.5) * (x[0] + x[1]), gy = T(0.5) * (y[0] + y[1]);
+    const T hx = T(0.5) * (x[3] + x[0]), hy = T(0.5) * (y[3] + y[0]);
+    T sa = T(0);
+    sa += (x[1] - gx) * (y[2] - gy) - (x[2] - gx) * (y[1] - gy);
+    sa += (x[2] - gx) * (y[3] - gy) - (x[3] - gx) * (y[2] - gy);
+    sa += (x[3] - gx) * (hy - gy) - (hx - gx) * (y[3] - gy);
+    const T Ap = T(0.5) * sa;
+    const T twoA = (x[2] - x[1]) * (y[3] - y[1]) - (x[3] - x[1]) * (y[2] - y[1]);
+    const T inv = T(1) / twoA;
+    const T bb[3] = {(y[2] - y[3]) * inv, (y[3] - y[1]) * inv, (y[1] - y[2]) * inv};
+    const T cc[3] = {(x[3] - x[2]) * inv, (x[1] - x[3]) * inv, (x[2] - x[1]) * inv};
+    T eps[3], sg[3];
+    strain<3>(bb, cc, u + 1, v + 1, eps);
+    hooke(p, eps, sg);
+    f[0] = f[1] = T(0);
+#pragma unroll
+    for (int i = 0; i < 3; ++i) {
+        const T tx = fmat(cc[i], sg[2], bb[i] * sg[0]);
+        const T ty = fmat(bb[i], sg[2], cc[i] * sg[1]);
+        f[2 * i + 2] = Ap * tx;
+        f[2 * i + 3] = Ap * ty;
+    }
+}
+
+// Through split: the two-node piece (nodes 1, 2), a bar along the uncut edge
+// carrying the area of the polygon mid(F), 1, 2, mid(edge 2-3).
+template <class T>
+__device__ __forceinline__ void bar_piece(const StepParamsT<T> &p, const T x[4], const T y[4], const T u[4],
+                                          const T v[4], T f[8]) {
+    const T gx = T(0.5) * (x[0] + x[1]), gy = T(0.5) * (y[0] + y[1]);
+    const T hx = T(0.5) * (x[2] + x[3]), hy = T(0.5) * (y[2] + y[3]);
+    T sa = T(0);
+    sa += (x[1] - gx) * (y[2] - gy) - (x[2] - gx) * (y[1] - gy);
+    sa += (x[2] - gx) * (hy - gy) - (hx - gx) * (y[2] - gy);
+    const T Ap = T(0.5) * sa;
+    const T dx = x[2] - x[1], dy = y[2] - y[1];
+    const T L2 = dx * dx + dy * dy;
+    const T dux = u[2] - u[1], duy = v[2] - v[1];
+    const T st = (dx * dux + dy * duy) / L2;
+    const T stress = p.E * st;
+    const T coef = Ap * stress / L2;
+    f[4] = coef * dx;
+    f[5] = coef * dy;
+    f[2] = -(coef * dx);
+    f[3] = -(coef * dy);
+}
 
 // Edge s of the structured grid (ids in ascending (smaller node, larger
 // node) order): its nodes and its neighbour elements (e0 the lower id, -1
@@ -305,6 +361,28 @@ __device__ __forceinline__ int64_t edge_h(int64_t i, int64_t j, int nx, int ny) 
 __device__ __forceinline__ int64_t edge_v(int64_t i, int64_t j, int nx) {
     const int64_t row = 2 * (int64_t)nx + 1;
     return j * row + (i < nx ? 2 * i + 1 : 2 * (int64_t)nx);
+}
+
+// Best-candidate order: larger G, then smaller element id, then smaller a.
+template <class T>
+__device__ __forceinline__ bool better(T g1, int e1, int a1, T g2, int e2, int a2) {
+    return g1 > g2 || (g1 == g2 && (e1 < e2 || (e1 == e2 && a1 < a2)));
+}
+
+// Prescribed velocity at time t: v0 times the ramp factor t / t_ramp
+// (evaluated in binary64 and rounded to T) while t < t_ramp.
+template <class T>
+__device__ __forceinline__ T prescribed(T v0, double t, double t_ramp) {
+    if (t_ramp > 0.0 && t < t_ramp) return v0 * T(t / t_ramp);
+    return v0;
+}
+
+__device__ __forceinline__ int perimeter_index(int i, int j, int nx, int ny) {
+    if (j == 0) return i;
+    if (j == ny) return (nx + 1) + i;
+    if (i == 0) return 2 * (nx + 1) + (j - 1);
+    if (i == nx) return 2 * (nx + 1) + (ny - 1) + (j - 1);
+    return -1;
 }
 
 // Load factor of the tractions at time t: piecewise linear through the

@@ -41,12 +41,6 @@ namespace mct {
 namespace {
 using namespace dev;
 
-// Best-candidate order: larger G, then smaller element id, then smaller a.
-template <class T>
-__device__ __forceinline__ bool better(T g1, int e1, int a1, T g2, int e2, int a2) {
-    return g1 > g2 || (g1 == g2 && (e1 < e2 || (e1 == e2 && a1 < a2)));
-}
-
 // A reduction value: the best accepted candidate (G, e, a, k) of a set, the
 // second largest accepted G (G2, -1 when the set has one) and the smallest
 // accepted G.
@@ -116,22 +110,6 @@ __device__ __forceinline__ void cand_block_reduce(CandT<T> &c, CandT<T> *red) {
         for (int w = 1; w < NT / 64; ++w)
             cand_merge<NEAR>(c, red[w].G, red[w].G2, red[w].Gmin, red[w].e, red[w].a, red[w].k);
     }
-}
-
-// Prescribed velocity at time t: v0 times the ramp factor t / t_ramp
-// (evaluated in binary64 and rounded to T) while t < t_ramp.
-template <class T>
-__device__ __forceinline__ T prescribed(T v0, double t, double t_ramp) {
-    if (t_ramp > 0.0 && t < t_ramp) return v0 * T(t / t_ramp);
-    return v0;
-}
-
-__device__ __forceinline__ int perimeter_index(int i, int j, int nx, int ny) {
-    if (j == 0) return i;
-    if (j == ny) return (nx + 1) + i;
-    if (i == 0) return 2 * (nx + 1) + (j - 1);
-    if (i == nx) return 2 * (nx + 1) + (ny - 1) + (j - 1);
-    return -1;
 }
 
 // Read-only data the whole launch shares (a batch's unit table and views,
