@@ -91,17 +91,17 @@ def bytes_per_step(cfgs, precision: int = 64, lattice: bool = False) -> int:
 # WRITE_SIZE x 1.0).  A figure holds for the kernel sources it was taken on
 # (their hash) and the tile shape; otherwise the traffic is reported as null.
 Q4_SOURCES = ("mct2d_step.hip", "mct2d_impl.h", "mct2d_device.h")
-TRI_SOURCES = ("mct2d_tri.hip", "mct2d_tri.h", "mct2d_front.h", "mct2d_device.h", "mct2d_impl.h")
+TRI_SOURCES = ("mct2d_resident_mesh.hip", "mct2d_resident_mesh_host.cpp", "mct2d_resident.h", "mct2d_exchange.h",
+               "mct2d_tri.h", "mct2d_device.h", "mct2d_impl.h")
 MEASURED_TRAFFIC = {
     # the batched lattice step kernel over the timed window (profiles/k_step_batch256_hbm_traffic.md)
     "batch256": {"sources": Q4_SOURCES, "sha256": "2d97f53763b48eab505aea9b89981113f334cd680da2a90911d3cdc5243f47e7",
                  "tile": 1, "fetch_kib": 286603.1083984375, "write_kib": 407268.94677734375},
-    # the fused triangle step on its automatic patches (profiles/k_fused_tri320k_hbm_traffic.md)
-    "tri320k": {"sources": TRI_SOURCES, "sha256": "34231779bbc88e9bb658b82c2b8f7abc29c19ab8067603c22b247d98007c4d92",
-                "tile": 5, "fetch_kib": 12160.925545, "write_kib": 5024.832886},
-    # the fused quadrilateral step on its automatic patches (profiles/k_fused_quad160k_kernel_trace.md)
-    "quad160k": {"sources": TRI_SOURCES, "sha256": "34231779bbc88e9bb658b82c2b8f7abc29c19ab8067603c22b247d98007c4d92",
-                 "tile": 5, "fetch_kib": 9238.957200, "write_kib": 5005.347145},
+    # the resident mesh step, per step of a launch of 512 (profiles/k_mesh_resident.md)
+    "tri320k": {"sources": TRI_SOURCES, "sha256": "af99620d799430c425ebe5cb5069ace69fafa017ecb89f289621803ee1ddf77c",
+                "tile": 5, "fetch_kib": 1158.0, "write_kib": 1160.1},
+    "quad160k": {"sources": TRI_SOURCES, "sha256": "af99620d799430c425ebe5cb5069ace69fafa017ecb89f289621803ee1ddf77c",
+                 "tile": 5, "fetch_kib": 1398.9, "write_kib": 1363.8},
 }
 FETCH_SCALE, WRITE_SCALE = 262144.0 / 131086.604, 262144.0 / 262144.0
 

@@ -2201,22 +2201,28 @@ static int autotune_unstructured(mct_ctx *c, int trial_steps, int *tile_out, int
     if ((rc = mct::tri::checkpoint(m, h, ck.data(), bytes, &bytes))) return rc;
     const int saved_kind = m.kernels;
     const bool saved_graph = m.use_graph;
-    m.use_graph = false;  // candidates are timed with direct launches
     float best = INFINITY;
     int best_kind = 1;
     const int nkinds = 5;
     hipEvent_t e0 = nullptr, e1 = nullptr;
     if (hipEventCreate(&e0) != hipSuccess || hipEventCreate(&e1) != hipSuccess) rc = MCT_EDEVICE;
-    for (int kind = 1; kind <= nkinds && rc == MCT_OK; ++kind) {
+    // choice 0 is the resident step, where it applies; the others are timed
+    // with direct launches
+    for (int kind = 0; kind <= nkinds && rc == MCT_OK; ++kind) {
+        if (kind == 0 && !saved_graph) continue;
+        m.use_graph = kind == 0;
         if ((rc = mct::tri::set_kernels(m, h, kind))) break;
+        if (kind == 0 && !m.res.threads) continue;
+        const int trial = kind == 0 ? std::max(trial_steps, 64) : trial_steps;
         if ((rc = mct::tri::restore(m, h, ck.data(), bytes))) break;
-        if ((rc = mct::tri::step(m, h, 2))) break;  // warm
+        if ((rc = mct::tri::step(m, h, kind == 0 ? mct::tri::kMeshResidentMinSteps : 2))) break;  // warm
         if (hipEventRecord(e0, c->stream) != hipSuccess) rc = MCT_EDEVICE;
-        if (!rc) rc = mct::tri::step(m, h, trial_steps);
+        if (!rc) rc = mct::tri::step(m, h, trial);
         if (!rc && hipEventRecord(e1, c->stream) != hipSuccess) rc = MCT_EDEVICE;
         if (!rc && hipEventSynchronize(e1) != hipSuccess) rc = MCT_EDEVICE;
         float ms = 0.f;
         if (!rc && hipEventElapsedTime(&ms, e0, e1) != hipSuccess) rc = MCT_EDEVICE;
+        ms /= (float)trial;
         if (!rc && ms < best) {
             best = ms;
             best_kind = kind;

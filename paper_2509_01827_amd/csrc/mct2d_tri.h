@@ -136,6 +136,60 @@ struct Eval {
     double *node_e;     // 2 per node: 1/2 m v.v, phi f_ext . u
 };
 
+// The resident step of a mesh (mct2d_resident_mesh.hip): n steps in one
+// cooperative launch, a patch of nodes per workgroup for all of them.
+constexpr int kMeshResidentSteps = 512;    // per launch, at most
+// Fewest steps per request: a resident launch costs 40 to 50 us beside its
+// steps (the cooperative launch, loading the state), saving 5 us a step on
+// 54 000 triangles, 9 on 320 000 and 13 on 160 000 quadrilaterals.
+constexpr int kMeshResidentMinSteps = 10;
+constexpr int kMeshResidentPatches = 256;  // one slot per polling lane
+// elements of a patch whose candidates the last wavefronts evaluate, and its
+// candidates that keep their path normals, by threads of the workgroup
+constexpr int mesh_cands(int threads) { return threads == 512 ? 192 : 96; }
+// LDS strides per element: strains (8 bytes), forces (16 bytes); gradients of
+// a ring edge (8 bytes)
+constexpr int kTriStrain = 3, kTriForce = 3, kQuadStrain = 13, kQuadForce = 5, kRingGrad = 9;
+constexpr int kMeshBc = 128;         // loaded or fixed nodes of a patch whose values stay in LDS
+
+// One patch: its nodes (own, then halo) in node_id[node0 ..], own-node tables
+// from own0, halo sources from halo0, its elements then its ring in the slot
+// tables from slot0, the ring's edges (quadrilaterals) from redge0.
+struct MeshPatch {
+    int32_t node0, own0, halo0, slot0, redge0;
+    int32_t nown, nhalo, nel, nring, nredge;
+};
+
+struct ResidentMesh {
+    int32_t threads = 0, npatch = 0, lds = 0;  // threads 0: not used
+    int32_t ne_max = 0, np_max = 0, nl_max = 0, nr_max = 0;  // LDS strides: strains, forces, nodes, ring edges
+    int32_t cap = 0, wmax = 0;  // nodes sent by a patch, elements at a node
+    int32_t o_u = 0, o_x = 0, o_q = 0, o_f = 0, o_rt = 0, o_rg = 0, o_cd = 0, o_cn = 0, o_ci = 0, o_bc = 0, o_cand = 0,
+            o_cslot = 0, o_cgc = 0, o_split = 0, o_code = 0;  // LDS offsets
+    const MeshPatch *patch = nullptr;
+    const int32_t *node_id = nullptr;       // global node ids
+    const int32_t *node_send = nullptr;     // own node: its first word in the exchange buffer, -1 not sent
+    const uint16_t *node_gather = nullptr;  // own node: 16 force places in colour order (the zero entry pads)
+    const int32_t *halo_src = nullptr;      // halo node: its first word
+    const uint32_t *slot_eid = nullptr;     // element id | kOwned
+    const uint2 *slot_lc = nullptr;         // its nodes in the patch, 16 bits each
+    const uint2 *slot_nb = nullptr;         // LDS place of the neighbour's strain across each edge
+    const uint2 *slot_code = nullptr;       // place of the neighbour's code (0xffff none)
+    const int4 *slot_far = nullptr;         // the neighbours' ids (-1 none)
+    const uint32_t *redge_eid = nullptr;
+    const uint2 *redge_lc = nullptr;
+    const uint32_t *redge_at = nullptr;     // LDS place of its strain | local edge << 16
+    uint64_t *xb = nullptr, *slots = nullptr;
+    uint32_t *err = nullptr;
+    void *tables = nullptr;  // the allocation that holds all of the above but err
+};
+// LDS layout and launch limits; np_max may be raised.
+bool mesh_resident_fits(ResidentMesh &r, int nv, int device);
+// n <= kMeshResidentSteps steps from ctl->base, u^base in buffer par0; takes
+// the epochs epoch0 .. epoch0 + n.
+hipError_t launch_mesh_resident(const Params &p, const ResidentMesh &r, int n, int par0, uint32_t epoch0,
+                                hipStream_t st);
+
 // One time step j of the running segment (step index ctl->base + j):
 // element forces and candidates, then nodal gather, update and the pick.
 hipError_t launch_step(const Params &p, int j, hipStream_t st);

@@ -76,8 +76,15 @@ void invalidate(Model &m) {
 }
 
 int read_ctl(Model &m, Host h, Ctl *out) {
-    TRY(h, hipMemcpyAsync(out, m.dctl, sizeof(Ctl), hipMemcpyDeviceToHost, h.stream));
+    // (behind it: the resident step's error word)
+    struct {
+        Ctl c;
+        uint32_t err[2];
+    } d;
+    TRY(h, hipMemcpyAsync(&d, m.dctl, sizeof d, hipMemcpyDeviceToHost, h.stream));
     TRY(h, hipStreamSynchronize(h.stream));
+    if (d.err[0]) return fail(h, MCT_EDEVICE, "resident step: a workgroup did not answer");
+    *out = d.c;
     return MCT_OK;
 }
 
@@ -374,13 +381,14 @@ int sized_patches(Model &m, Host h, int *P_out, int32_t *emax) {
 
 // Step kernels from the requested choice: 1 split kernels; 2, 3, 4 the fused
 // kernel on patches of 64, 128, 256 nodes; 5 and 0 (automatic) the fused
-// kernel on patches of the size sized_patches finds, and 0 (automatic) the
-// same.  A fused choice whose tables do not fit runs the split kernels.
+// kernel on patches of the size sized_patches finds, 0 with the resident step
+// in front of it where that applies.  A fused choice whose tables do not fit runs the split kernels.
 int choose_kernels(Model &m, Host h) {
     Params &p = m.prm;
     p.patch_emax = 0;
     p.patch_nodes = 0;
     p.fold = 0;
+    TRY(h, plan_resident(m, h.stream));
     int P = 0;
     if (m.kernels >= 2 && m.kernels <= 4)
         P = 64 << (m.kernels - 2);
@@ -424,6 +432,7 @@ int choose_kernels(Model &m, Host h) {
 void release(Model &m) {
     if (m.graph) (void)hipGraphExecDestroy(m.graph);
     m.graph = nullptr;
+    free_resident(m);
     dfree(m.dconn);
     dfree(m.dnbr);
     dfree(m.dopp);
@@ -901,7 +910,7 @@ int finalize(Model &m, Host h) {
         }
     }
     TRY(h, hipMalloc((void **)&m.dlog, sizeof(LogRec) * ne));
-    TRY(h, hipMalloc((void **)&m.dctl, sizeof(Ctl)));
+    TRY(h, hipMalloc((void **)&m.dctl, sizeof(Ctl) + 8));
     // start tip of single-tip tracking: given, or the one path end of the
     // pre-notch (an entry or exit edge of a notch element whose neighbour
     // across it is intact)
@@ -929,6 +938,7 @@ int finalize(Model &m, Host h) {
     Ctl c0{};
     c0.tip = tip;
     TRY(h, hipMemcpyAsync(m.dctl, &c0, sizeof c0, hipMemcpyHostToDevice, h.stream));
+    TRY(h, hipMemsetAsync(m.dctl + 1, 0, 8, h.stream));
     Params &p = m.prm;
     p = Params{};
     p.nn = (int32_t)nn;
@@ -1006,6 +1016,18 @@ int step(Model &m, Host h, int64_t n) {
     if (!m.finalized) return fail(h, MCT_ESTATE, "finalize first");
     if (n < 0) return fail(h, MCT_EINVAL, "negative step count");
     int64_t left = n;
+    hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
+    if (m.use_graph && m.res.threads && n >= kMeshResidentMinSteps &&
+        hipStreamIsCapturing(h.stream, &cap) == hipSuccess && cap == hipStreamCaptureStatusNone) {
+        while (left > 0) {
+            const int k = (int)std::min<int64_t>(left, kMeshResidentSteps);
+            TRY(h, launch_mesh_resident(m.prm, m.res, k, (int)(m.steps_enqueued & 1), m.res_epoch, h.stream));
+            m.res_epoch += (uint32_t)k;
+            m.steps_enqueued += k;
+            left -= k;
+        }
+        return MCT_OK;
+    }
     if (m.use_graph) {
         while (left >= kGraphSteps) {
             if (!m.graph) {

@@ -85,6 +85,8 @@ struct Model {
     uint8_t *dtipflag = nullptr;
     hipGraphExec_t graph = nullptr;
     int64_t steps_enqueued = 0;
+    ResidentMesh res;        // the resident step's patches (automatic kernels, where they fit)
+    uint32_t res_epoch = 0;  // of the state in memory (exchange tags)
 };
 
 // Every function returns an mct status and writes a message to err on
@@ -95,6 +97,8 @@ struct Host {
 };
 
 void release(Model &m);
+void free_resident(Model &m);
+hipError_t plan_resident(Model &m, hipStream_t stream);
 // nv = 3: triangles (3 nodes per element); nv = 4: convex quadrilaterals.
 int set_mesh(Model &m, Host h, int nv, int64_t nn, const double *X, const double *Y, int64_t ne,
              const int32_t *conn);
