@@ -303,6 +303,10 @@ int mct_sync(mct_ctx *ctx);
 
 int mct_get_info(mct_ctx *ctx, mct_info *out);
 
+/* Numbers of nodes, elements and edges of the model (a batch: of the selected
+ * specimen), without waiting for the device. */
+int mct_get_sizes(mct_ctx *ctx, int64_t out[3]);
+
 /* Split log in the order the splits were made: step index k (the split was
  * decided on the state at t_k and acts from step k+1), element id, entry
  * and exit local edges, G of the chosen path.  Any output may be NULL. */

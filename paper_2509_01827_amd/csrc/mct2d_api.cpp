@@ -18,6 +18,7 @@
 #include <string>
 #include <vector>
 
+#include "mct2d_fetch.h"
 #include "mct2d_impl.h"
 #include "mct2d_tri_host.h"
 
@@ -142,6 +143,7 @@ struct mct_ctx {
     // epochs its launches have taken
     mct::ResidentPlan res{};
     uint32_t res_epoch = 0;
+    mct::Fetch fetch;  // query results to the host
 
     // state queries
     bool ev_alloc = false;
@@ -934,8 +936,10 @@ int read_control(mct_ctx *c, int s, Control *h) {
         uint32_t err[4];
     } v;
     const bool res = c->res.threads != 0;
-    HIP_TRY(c, hipMemcpyAsync(&v, c->dctl + s, res ? sizeof v : sizeof(Control), hipMemcpyDeviceToHost, c->stream));
-    HIP_TRY(c, hipStreamSynchronize(c->stream));
+    const mct::Fetch::Part part{c->dctl + s, res ? sizeof v : sizeof(Control)};
+    HIP_TRY(c, c->fetch.run(c->stream, &part, 1, &v, sizeof v, [&](int, size_t off, const char *d, size_t n) {
+        std::memcpy(reinterpret_cast<char *>(&v) + off, d, n);
+    }));
     *h = v.ctl;
     if (res && v.err[0])
         return fail(c, MCT_EDEVICE, "resident step: a workgroup did not answer (step %lld)", (long long)v.ctl.base);
@@ -1627,6 +1631,9 @@ int mct_finalize(mct_ctx *c) {
         }
     }
     c->steps_enqueued = 0;
+    int64_t nn_max = 0;
+    for (const Spec &s : c->specs) nn_max = std::max(nn_max, s.nn);
+    c->fetch.reserve(sizeof(double) * 2 * (size_t)nn_max + 256);
     return MCT_OK;
 }
 
@@ -1764,6 +1771,21 @@ int mct_sync(mct_ctx *c) {
     return MCT_OK;
 }
 
+int mct_get_sizes(mct_ctx *c, int64_t out[3]) {
+    if (!c || !out) return MCT_EINVAL;
+    if (c->tri) {
+        out[0] = c->tri->nn;
+        out[1] = c->tri->ne;
+        out[2] = c->tri->ns;
+        return MCT_OK;
+    }
+    const Spec &s = cur(c);
+    out[0] = s.nn;
+    out[1] = s.ne;
+    out[2] = s.ns;
+    return MCT_OK;
+}
+
 int mct_get_info(mct_ctx *c, mct_info *out) {
     if (!c || !out) return MCT_EINVAL;
     TRI_FWD(c, get_info, out);
@@ -1887,6 +1909,28 @@ int mct_get_field(mct_ctx *c, int which, int64_t cap, double *out) {
     int rc = widen_state(c);
     if (rc) return rc;
     Control h;
+    if (which < MCT_FIELD_A) {
+        // the field of the steps enqueued, with the control block in front: should
+        // the device have stopped short of them, its error is returned
+        struct {
+            Control ctl;
+            uint32_t err[4];
+        } v{};
+        const bool u = which == MCT_FIELD_U, odd = (c->steps_enqueued & 1) != 0;
+        const bool res = c->res.threads != 0;
+        const mct::Fetch::Part parts[3] = {
+            {c->dctl + c->sel, res ? sizeof v : sizeof(Control)},
+            {u ? (odd ? s.prm.ux1 : s.prm.ux0) : s.prm.vx, sizeof(double) * s.nn},
+            {u ? (odd ? s.prm.uy1 : s.prm.uy0) : s.prm.vy, sizeof(double) * s.nn}};
+        char *const to[3] = {reinterpret_cast<char *>(&v), reinterpret_cast<char *>(out),
+                             reinterpret_cast<char *>(out + s.nn)};
+        HIP_TRY(c, c->fetch.run(c->stream, parts, 3, out, sizeof(double) * 2 * s.nn, [&](int i, size_t off, const char *d, size_t n) {
+            std::memcpy(to[i] + off, d, n);
+        }));
+        if (res && v.err[0])
+            return fail(c, MCT_EDEVICE, "resident step: a workgroup did not answer (step %lld)", (long long)v.ctl.base);
+        if (((v.ctl.base ^ c->steps_enqueued) & 1) == 0) return MCT_OK;
+    }
     if ((rc = read_control(c, c->sel, &h))) return rc;
     if (which >= MCT_FIELD_A) {
         if ((rc = ensure_eval(c))) return rc;
@@ -1981,8 +2025,10 @@ int mct_get_split_codes(mct_ctx *c, int64_t cap, uint8_t *out) {
     if (!c->finalized) return fail(c, MCT_ESTATE, "finalize first");
     const Spec &s = cur(c);
     if (cap < s.ne) return fail(c, MCT_ECAPACITY, "need %lld bytes", (long long)s.ne);
-    HIP_TRY(c, hipMemcpyAsync(out, s.prm.split, (size_t)s.ne, hipMemcpyDeviceToHost, c->stream));
-    HIP_TRY(c, hipStreamSynchronize(c->stream));
+    const mct::Fetch::Part part{s.prm.split, (size_t)s.ne};
+    HIP_TRY(c, c->fetch.run(c->stream, &part, 1, out, (size_t)s.ne, [&](int, size_t off, const char *d, size_t n) {
+        std::memcpy(out + off, d, n);
+    }));
     return MCT_OK;
 }
 

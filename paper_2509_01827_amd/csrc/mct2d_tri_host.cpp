@@ -81,8 +81,10 @@ int read_ctl(Model &m, Host h, Ctl *out) {
         Ctl c;
         uint32_t err[2];
     } d;
-    TRY(h, hipMemcpyAsync(&d, m.dctl, sizeof d, hipMemcpyDeviceToHost, h.stream));
-    TRY(h, hipStreamSynchronize(h.stream));
+    const Fetch::Part part{m.dctl, sizeof d};
+    TRY(h, m.fetch.run(h.stream, &part, 1, &d, sizeof d, [&](int, size_t off, const char *p, size_t n) {
+        std::memcpy(reinterpret_cast<char *>(&d) + off, p, n);
+    }));
     if (d.err[0]) return fail(h, MCT_EDEVICE, "resident step: a workgroup did not answer");
     *out = d.c;
     return MCT_OK;
@@ -1008,6 +1010,7 @@ int finalize(Model &m, Host h) {
     if (m.dt > m.dt_limit)
         return fail(h, MCT_ESTABILITY, "dt = %g exceeds the stability limit 2/omega_max = %g", m.dt, m.dt_limit);
     m.steps_enqueued = 0;
+    m.fetch.reserve(sizeof(double) * 2 * (size_t)m.nn + 256);
     m.finalized = true;
     return MCT_OK;
 }
@@ -1168,16 +1171,31 @@ int get_field(Model &m, Host h, int which, int64_t cap, double *out) {
     if (which < MCT_FIELD_U || which > MCT_FIELD_PRINCIPAL) return fail(h, MCT_EINVAL, "unknown field %d", which);
     if (cap < need) return fail(h, MCT_ECAPACITY, "field needs %lld values", (long long)need);
     if (which == MCT_FIELD_U || which == MCT_FIELD_V) {
-        Ctl c0;
-        int rc0 = read_ctl(m, h, &c0);
-        if (rc0) return rc0;
-        std::vector<double> buf(2 * nn);
-        TRY(h, hipMemcpyAsync(buf.data(), which == MCT_FIELD_U ? m.du[c0.base & 1] : m.dv, sizeof(double) * 2 * nn,
-                              hipMemcpyDeviceToHost, h.stream));
-        TRY(h, hipStreamSynchronize(h.stream));
-        for (int64_t i = 0; i < nn; ++i) {
-            out[i] = buf[2 * i];
-            out[nn + i] = buf[2 * i + 1];
+        // the field of the steps enqueued, with the control block in front: should
+        // the device have stopped short of them, its error is returned
+        int64_t at = m.steps_enqueued;
+        for (int tries = 0; tries < 2; ++tries) {
+            struct {
+                Ctl c;
+                uint32_t err[2];
+            } d{};
+            const Fetch::Part parts[2] = {{m.dctl, sizeof d},
+                                          {which == MCT_FIELD_U ? m.du[at & 1] : m.dv, sizeof(double) * 2 * nn}};
+            TRY(h, m.fetch.run(h.stream, parts, 2, out, sizeof(double) * 2 * nn, [&](int i, size_t off, const char *p, size_t n) {
+                if (i == 0) {
+                    std::memcpy(reinterpret_cast<char *>(&d) + off, p, n);
+                    return;
+                }
+                const double *xy = reinterpret_cast<const double *>(p);
+                double *const x = out + off / 16, *const y = x + nn;
+                for (size_t q = 0; q < n / 16; ++q) {
+                    x[q] = xy[2 * q];
+                    y[q] = xy[2 * q + 1];
+                }
+            }));
+            if (d.err[0]) return fail(h, MCT_EDEVICE, "resident step: a workgroup did not answer");
+            if (((d.c.base ^ at) & 1) == 0) break;
+            at = d.c.base;
         }
         return MCT_OK;
     }
@@ -1243,8 +1261,10 @@ int get_energies(Model &m, Host h, double out[4]) {
 int get_split_codes(Model &m, Host h, int64_t cap, uint8_t *out) {
     if (!m.finalized) return fail(h, MCT_ESTATE, "finalize first");
     if (cap < m.ne) return fail(h, MCT_ECAPACITY, "need %lld bytes", (long long)m.ne);
-    TRY(h, hipMemcpyAsync(out, m.dsplit, m.ne, hipMemcpyDeviceToHost, h.stream));
-    TRY(h, hipStreamSynchronize(h.stream));
+    const Fetch::Part part{m.dsplit, (size_t)m.ne};
+    TRY(h, m.fetch.run(h.stream, &part, 1, out, (size_t)m.ne, [&](int, size_t off, const char *p, size_t n) {
+        std::memcpy(out + off, p, n);
+    }));
     return MCT_OK;
 }
 

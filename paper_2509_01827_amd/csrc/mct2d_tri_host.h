@@ -11,6 +11,7 @@
 #include <vector>
 
 #include "../../include/mct2d.h"
+#include "mct2d_fetch.h"
 #include "mct2d_tri.h"
 
 namespace mct {
@@ -87,6 +88,7 @@ struct Model {
     int64_t steps_enqueued = 0;
     ResidentMesh res;        // the resident step's patches (automatic kernels, where they fit)
     uint32_t res_epoch = 0;  // of the state in memory (exchange tags)
+    Fetch fetch;             // query results to the host
 };
 
 // Every function returns an mct status and writes a message to err on

@@ -53,7 +53,7 @@ EXPORTS = [
     "mct_mlp_forward", "mct_mlp_gradient", "mct_mlp_train_step", "mct_get_energies", "mct_set_tracking",
     "mct_set_load_curve", "mct_set_mesh_tri", "mct_set_mesh_q4", "mct_set_front_pick",
     "mct_set_smoothing", "mct_bind_device_buffers", "mct_set_lattice", "mct_get_lattice",
-    "mct_set_near_log", "mct_get_near_log", "mct_profile_step", "mct_get_tips_noalloc",
+    "mct_set_near_log", "mct_get_near_log", "mct_profile_step", "mct_get_tips_noalloc", "mct_get_sizes",
 ]
 LATTICE_AUTO = 0
 LATTICE_GENERAL = 1
@@ -115,6 +115,7 @@ def load() -> C.CDLL:
     L.mct_step.argtypes = [P, C.c_int64]
     L.mct_sync.argtypes = [P]
     L.mct_get_info.argtypes = [P, C.POINTER(Info)]
+    L.mct_get_sizes.argtypes = [P, C.POINTER(C.c_int64)]
     L.mct_get_crack_set.argtypes = [P, C.c_int64, P, P, P, P, P, C.POINTER(C.c_int64)]
     L.mct_get_tips.argtypes = [P, C.c_int64, P, P, C.POINTER(C.c_int64)]
     L.mct_get_field.argtypes = [P, C.c_int, C.c_int64, dp]
@@ -392,6 +393,12 @@ class Model:
         self._check(self._L.mct_get_info(self._h, C.byref(inf)), "get_info")
         return {k: getattr(inf, k) for k, _ in Info._fields_}
 
+    def _sizes(self):
+        """Nodes, elements and edges (no device synchronisation)."""
+        out = (C.c_int64 * 3)()
+        self._check(self._L.mct_get_sizes(self._h, out), "get_sizes")
+        return out[0], out[1], out[2]
+
     def crack_set(self) -> dict:
         cnt = C.c_int64(0)
         rc = self._L.mct_get_crack_set(self._h, 0, None, None, None, None, None, C.byref(cnt))
@@ -419,10 +426,9 @@ class Model:
     def field(self, which=FIELD_U):
         """Nodal fields (U, V, A, FINT) as (x, y); SIGMA_EDGE as [n_edges][3];
         PRINCIPAL as [n_elems]."""
-        inf = self.info()
-        nn, ne, ns = inf["n_nodes"], inf["n_elems"], inf["n_edges"]
+        nn, ne, ns = self._sizes()
         n = {FIELD_SIGMA_EDGE: 3 * ns, FIELD_PRINCIPAL: ne}.get(which, 2 * nn)
-        out = np.zeros(n)
+        out = np.empty(n)
         self._check(self._L.mct_get_field(self._h, int(which), n, out), "get_field")
         if which == FIELD_SIGMA_EDGE:
             return out.reshape(3, ns).T.copy()
@@ -444,8 +450,8 @@ class Model:
         return out.reshape(len(elems), 4, 3, 3)
 
     def split_codes(self):
-        ne = self.info()["n_elems"]
-        out = np.zeros(ne, np.uint8)
+        ne = self._sizes()[1]
+        out = np.empty(ne, np.uint8)
         self._check(self._L.mct_get_split_codes(self._h, ne, out), "get_split_codes")
         return out
 
