@@ -290,12 +290,14 @@ __global__ __launch_bounds__(kBlk) void k_fill_u32(uint32_t *a, int64_t n, uint3
 constexpr int kRows = 32;
 constexpr int kIn = 32;  // padded input width
 
-__device__ __forceinline__ float gelu_f(float z) { return 0.5f * z * (1.0f + erff(z * 0.70710678118654752f)); }
-__device__ __forceinline__ float gelu_d(float z) {
-    const float Phi = 0.5f * (1.0f + erff(z * 0.70710678118654752f));
+// GELU of z and, for the gradient, its derivative (one erf for both).
+__device__ __forceinline__ float gelu(float z, float e) { return 0.5f * z * (1.0f + e); }
+__device__ __forceinline__ float gelu_slope(float z, float e) {
+    const float Phi = 0.5f * (1.0f + e);
     const float phi = expf(-0.5f * z * z) * 0.39894228040143268f;
     return Phi + z * phi;
 }
+__device__ __forceinline__ float gelu_erf(float z) { return erff(z * 0.70710678118654752f); }
 __device__ __forceinline__ __bf16 to_bf(float v) { return (__bf16)v; }
 __device__ __forceinline__ float from_bf(__bf16 v) { return (float)v; }
 
@@ -305,10 +307,23 @@ struct MlpShared {
     __bf16 w3[kHidden];
     float b1[kHidden], b2[kHidden];
     float b3;
-    __bf16 x[kRows * kIn];         // [row][k]
-    __bf16 h1[kRows * kHidden];    // [row][m]
-    __bf16 dz[kRows * kHidden];    // dZ2, then dZ1 [row][n]
 };
+
+// One wavefront's rows.
+struct MlpTile {
+    alignas(16) __bf16 x[kRows * kIn];  // [row][k]
+    __bf16 h1[kRows * kHidden];         // [row][m]
+};
+struct MlpTrainTile : MlpTile {
+    __bf16 dz[kRows * kHidden];  // dZ2, then dZ1 [row][n]
+};
+
+// Orders a wavefront's accesses to its own tile: LDS serves a wavefront in
+// order, so only the compiler has to keep to it.
+__device__ __forceinline__ void tile_sync() {
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+}
 
 __device__ void load_weights(const MlpDev &m, MlpShared &sh) {
     // 16-byte copies (8 bfloat16 each); the arrays are 256-byte aligned
@@ -327,31 +342,34 @@ __device__ void load_weights(const MlpDev &m, MlpShared &sh) {
     if (threadIdx.x == 0) sh.b3 = m.master[kOffB3];
 }
 
-__device__ void load_rows(const float *X, int64_t r0, int64_t n, MlpShared &sh) {
-    for (int i = threadIdx.x; i < kRows * kIn; i += blockDim.x) {
+__device__ void load_rows(const float *X, int64_t r0, int64_t n, MlpTile &tl) {
+    for (int i = threadIdx.x & 63; i < kRows * kIn; i += 64) {
         const int r = i / kIn, k = i % kIn;
         float v = 0.0f;
         if (k < kFeat && r0 + r < n) v = X[(r0 + r) * kFeat + k];
-        sh.x[i] = to_bf(v);
+        tl.x[i] = to_bf(v);
     }
 }
 
 // Forward pass of one 32-row tile.  Leaves h1 in LDS and returns in
-// registers z1, z2 (D layout) and the logit of this lane's rows (all 16
-// lanes of a row group hold the sum).
+// registers the logit of this lane's rows (all 16 lanes of a row group hold
+// the sum) and, GRAD, the slopes of both GELU layers and the second hidden
+// layer (D layout).
 struct Fwd {
-    float z1[2][4][4], z2[2][4][4], h2[2][4][4];
+    float d1[2][4][4], d2[2][4][4];
+    __bf16 h2[2][4][4];
     float z3[2][4];
 };
 
-__device__ void forward_tile(MlpShared &sh, Fwd &f) {
+template <bool GRAD>
+__device__ __forceinline__ void forward_tile(const MlpShared &sh, MlpTile &tl, Fwd &f) {
     const int l = threadIdx.x & 63, r16 = l & 15, kq = 8 * (l >> 4), rq = 4 * (l >> 4);
     // layer 1
 #pragma unroll
     for (int h = 0; h < 2; ++h) {
         bf16x8 a;
 #pragma unroll
-        for (int i = 0; i < 8; ++i) a[i] = sh.x[(16 * h + r16) * kIn + kq + i];
+        for (int i = 0; i < 8; ++i) a[i] = tl.x[(16 * h + r16) * kIn + kq + i];
 #pragma unroll
         for (int t = 0; t < 4; ++t) {
             bf16x8 b;
@@ -362,12 +380,13 @@ __device__ void forward_tile(MlpShared &sh, Fwd &f) {
 #pragma unroll
             for (int i = 0; i < 4; ++i) {
                 const float z = acc[i] + sh.b1[16 * t + r16];
-                f.z1[h][t][i] = z;
-                sh.h1[(16 * h + rq + i) * kHidden + 16 * t + r16] = to_bf(gelu_f(z));
+                const float e = gelu_erf(z);
+                if (GRAD) f.d1[h][t][i] = gelu_slope(z, e);
+                tl.h1[(16 * h + rq + i) * kHidden + 16 * t + r16] = to_bf(gelu(z, e));
             }
         }
     }
-    __syncthreads();
+    tile_sync();
     // layer 2 and the output layer
 #pragma unroll
     for (int h = 0; h < 2; ++h) {
@@ -380,7 +399,7 @@ __device__ void forward_tile(MlpShared &sh, Fwd &f) {
                 bf16x8 a, b;
 #pragma unroll
                 for (int i = 0; i < 8; ++i) {
-                    a[i] = sh.h1[(16 * h + r16) * kHidden + 32 * kc + kq + i];
+                    a[i] = tl.h1[(16 * h + r16) * kHidden + 32 * kc + kq + i];
                     b[i] = sh.w2[(32 * kc + kq + i) * kHidden + 16 * t + r16];
                 }
                 acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, b, acc, 0, 0, 0);
@@ -388,10 +407,13 @@ __device__ void forward_tile(MlpShared &sh, Fwd &f) {
 #pragma unroll
             for (int i = 0; i < 4; ++i) {
                 const float z = acc[i] + sh.b2[16 * t + r16];
-                f.z2[h][t][i] = z;
-                const float hv = from_bf(to_bf(gelu_f(z)));
-                f.h2[h][t][i] = hv;
-                part[i] += hv * from_bf(sh.w3[16 * t + r16]);
+                const float e = gelu_erf(z);
+                const __bf16 hv = to_bf(gelu(z, e));
+                if (GRAD) {
+                    f.d2[h][t][i] = gelu_slope(z, e);
+                    f.h2[h][t][i] = hv;
+                }
+                part[i] += from_bf(hv) * from_bf(sh.w3[16 * t + r16]);
             }
         }
 #pragma unroll
@@ -404,20 +426,29 @@ __device__ void forward_tile(MlpShared &sh, Fwd &f) {
     }
 }
 
-__global__ __launch_bounds__(64) void k_mlp_fwd(MlpDev m, const float *X, const int32_t *n_dev, int64_t n_host,
-                                                float *logits, const int32_t *cand, uint32_t *screen, float tau,
-                                                unsigned long long *stats) {
+// Four wavefronts per workgroup share the weights, each with its own tiles: one
+// tile is a chain of some 10 us, so four per SIMD are under way.  65 536 rows:
+// 29 us with one wavefront per workgroup, 19 with four.
+constexpr int kFwdWaves = 4;
+__global__ __launch_bounds__(64 * kFwdWaves) void k_mlp_fwd(MlpDev m, const float *X, const int32_t *n_dev,
+                                                            int64_t n_host, float *logits, const int32_t *cand,
+                                                            uint32_t *screen, float tau, unsigned long long *stats) {
     __shared__ MlpShared sh;
+    __shared__ MlpTile s_tile[kFwdWaves];
     const int64_t n = n_dev ? (int64_t)*n_dev : n_host;
     load_weights(m, sh);
-    const int l = threadIdx.x, r16 = l & 15, rq = 4 * (l >> 4);
+    __syncthreads();
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    MlpTile &tl = s_tile[wave];
+    const int l = threadIdx.x & 63, r16 = l & 15, rq = 4 * (l >> 4);
     uint8_t *bytes = reinterpret_cast<uint8_t *>(screen);
-    for (int64_t r0 = (int64_t)blockIdx.x * kRows; r0 < n; r0 += (int64_t)gridDim.x * kRows) {
-        __syncthreads();  // weights loaded / previous tile consumed
-        load_rows(X, r0, n, sh);
-        __syncthreads();
+    for (int64_t r0 = ((int64_t)wave * gridDim.x + blockIdx.x) * kRows; r0 < n;
+         r0 += (int64_t)kFwdWaves * gridDim.x * kRows) {
+        tile_sync();  // previous tile consumed
+        load_rows(X, r0, n, tl);
+        tile_sync();
         Fwd f;
-        forward_tile(sh, f);
+        forward_tile<false>(sh, tl, f);
         int flagged = 0;
         if (r16 == 0) {
 #pragma unroll
@@ -445,11 +476,27 @@ __global__ __launch_bounds__(64) void k_mlp_fwd(MlpDev m, const float *X, const 
 
 // Gradient of the mean weighted logistic loss, one partial per workgroup:
 // partials[b * (kParams + 1) + q], q = kParams is the loss.
-__global__ __launch_bounds__(64) void k_mlp_train(MlpDev m, const float *X, const float *Y, int64_t n,
-                                                  float pos_weight, float *partials) {
-    __shared__ MlpShared sh;
+//
+// A tile of 32 rows is one long chain for its wavefront (LDS, MFMA and some 130
+// erf per lane, 25 us), so what counts is how many are under way: four
+// wavefronts per workgroup share the weights, each with its own rows, and add
+// their sums up in order at the end.  65 536 rows: 111 us with one wavefront per workgroup, 64 with four.
+constexpr int kTrainWaves = 4;
+__global__ __launch_bounds__(64 * kTrainWaves) void k_mlp_train(MlpDev m, const float *X, const float *Y, int64_t n,
+                                                                float pos_weight, float *partials) {
+    struct Work {
+        MlpShared sh;
+        MlpTrainTile tile[kTrainWaves];
+    };
+    constexpr size_t kSum = sizeof(float) * (kParams + 1);
+    __shared__ __attribute__((aligned(16))) char s_mem[sizeof(Work) > kSum ? sizeof(Work) : kSum];
+    Work &wk = *reinterpret_cast<Work *>(s_mem);
+    MlpShared &sh = wk.sh;
     load_weights(m, sh);
-    const int l = threadIdx.x, r16 = l & 15, kq = 8 * (l >> 4), rq = 4 * (l >> 4);
+    __syncthreads();
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    MlpTrainTile &tl = wk.tile[wave];
+    const int l = threadIdx.x & 63, r16 = l & 15, kq = 8 * (l >> 4), rq = 4 * (l >> 4);
     const float inv_n = 1.0f / (float)n;
     f32x4 gW2[4][4], gW1[4];
 #pragma unroll
@@ -460,12 +507,13 @@ __global__ __launch_bounds__(64) void k_mlp_train(MlpDev m, const float *X, cons
     }
     float gb1[4] = {0, 0, 0, 0}, gb2[4] = {0, 0, 0, 0}, gw3[4] = {0, 0, 0, 0};
     float gb3 = 0.0f, loss = 0.0f;
-    for (int64_t r0 = (int64_t)blockIdx.x * kRows; r0 < n; r0 += (int64_t)gridDim.x * kRows) {
-        __syncthreads();
-        load_rows(X, r0, n, sh);
-        __syncthreads();
+    for (int64_t r0 = ((int64_t)wave * gridDim.x + blockIdx.x) * kRows; r0 < n;
+         r0 += (int64_t)kTrainWaves * gridDim.x * kRows) {
+        tile_sync();
+        load_rows(X, r0, n, tl);
+        tile_sync();
         Fwd f;
-        forward_tile(sh, f);
+        forward_tile<true>(sh, tl, f);
         // output layer and dZ2
 #pragma unroll
         for (int h = 0; h < 2; ++h)
@@ -485,25 +533,25 @@ __global__ __launch_bounds__(64) void k_mlp_train(MlpDev m, const float *X, cons
 #pragma unroll
                 for (int t = 0; t < 4; ++t) {
                     const int col = 16 * t + r16;
-                    gw3[t] += f.h2[h][t][i] * dz3;
+                    gw3[t] += from_bf(f.h2[h][t][i]) * dz3;
                     const float dh2 = dz3 * from_bf(sh.w3[col]);
-                    const __bf16 dz2 = to_bf(dh2 * gelu_d(f.z2[h][t][i]));
+                    const __bf16 dz2 = to_bf(dh2 * f.d2[h][t][i]);
                     gb2[t] += from_bf(dz2);
-                    sh.dz[(16 * h + rq + i) * kHidden + col] = dz2;
+                    tl.dz[(16 * h + rq + i) * kHidden + col] = dz2;
                 }
             }
-        __syncthreads();
+        tile_sync();
         // gW2 += H1^T dZ2 (K = the 32 rows of the tile)
 #pragma unroll
         for (int tm = 0; tm < 4; ++tm) {
             bf16x8 a;
 #pragma unroll
-            for (int i = 0; i < 8; ++i) a[i] = sh.h1[(kq + i) * kHidden + 16 * tm + r16];
+            for (int i = 0; i < 8; ++i) a[i] = tl.h1[(kq + i) * kHidden + 16 * tm + r16];
 #pragma unroll
             for (int tn = 0; tn < 4; ++tn) {
                 bf16x8 b;
 #pragma unroll
-                for (int i = 0; i < 8; ++i) b[i] = sh.dz[(kq + i) * kHidden + 16 * tn + r16];
+                for (int i = 0; i < 8; ++i) b[i] = tl.dz[(kq + i) * kHidden + 16 * tn + r16];
                 gW2[tm][tn] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, b, gW2[tm][tn], 0, 0, 0);
             }
         }
@@ -519,36 +567,36 @@ __global__ __launch_bounds__(64) void k_mlp_train(MlpDev m, const float *X, cons
                     bf16x8 a, b;
 #pragma unroll
                     for (int i = 0; i < 8; ++i) {
-                        a[i] = sh.dz[(16 * h + r16) * kHidden + 32 * kc + kq + i];
+                        a[i] = tl.dz[(16 * h + r16) * kHidden + 32 * kc + kq + i];
                         b[i] = sh.w2[(16 * tm + r16) * kHidden + 32 * kc + kq + i];
                     }
                     acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, b, acc, 0, 0, 0);
                 }
 #pragma unroll
                 for (int i = 0; i < 4; ++i) {
-                    const __bf16 v = to_bf(acc[i] * gelu_d(f.z1[h][tm][i]));
+                    const __bf16 v = to_bf(acc[i] * f.d1[h][tm][i]);
                     dz1v[h][tm][i] = v;
                     gb1[tm] += from_bf(v);
                 }
             }
-        __syncthreads();
+        tile_sync();
 #pragma unroll
         for (int h = 0; h < 2; ++h)
 #pragma unroll
             for (int tm = 0; tm < 4; ++tm)
 #pragma unroll
-                for (int i = 0; i < 4; ++i) sh.dz[(16 * h + rq + i) * kHidden + 16 * tm + r16] = dz1v[h][tm][i];
-        __syncthreads();
+                for (int i = 0; i < 4; ++i) tl.dz[(16 * h + rq + i) * kHidden + 16 * tm + r16] = dz1v[h][tm][i];
+        tile_sync();
         // gW1 += X^T dZ1 (input rows padded to 16)
         {
             bf16x8 a;
 #pragma unroll
-            for (int i = 0; i < 8; ++i) a[i] = sh.x[(kq + i) * kIn + r16];
+            for (int i = 0; i < 8; ++i) a[i] = tl.x[(kq + i) * kIn + r16];
 #pragma unroll
             for (int tn = 0; tn < 4; ++tn) {
                 bf16x8 b;
 #pragma unroll
-                for (int i = 0; i < 8; ++i) b[i] = sh.dz[(kq + i) * kHidden + 16 * tn + r16];
+                for (int i = 0; i < 8; ++i) b[i] = tl.dz[(kq + i) * kHidden + 16 * tn + r16];
                 gW1[tn] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, b, gW1[tn], 0, 0, 0);
             }
         }
@@ -568,42 +616,74 @@ __global__ __launch_bounds__(64) void k_mlp_train(MlpDev m, const float *X, cons
         gb3 += __shfl_xor(gb3, off, 64);
         loss += __shfl_xor(loss, off, 64);
     }
-    float *out = partials + (int64_t)blockIdx.x * (kParams + 1);
-#pragma unroll
-    for (int tn = 0; tn < 4; ++tn)
-#pragma unroll
-        for (int i = 0; i < 4; ++i) {
-            const int row = rq + i;
-            if (row < kFeat) out[row * kHidden + 16 * tn + r16] = gW1[tn][i];
-        }
-#pragma unroll
-    for (int tm = 0; tm < 4; ++tm)
+    // the wavefronts' sums, in order
+    float *const sum = reinterpret_cast<float *>(s_mem);
+    for (int w = 0; w < kTrainWaves; ++w) {
+        __syncthreads();
+        if (w != wave) continue;
+        auto add = [&](int q, float v) { sum[q] = w == 0 ? v : sum[q] + v; };
 #pragma unroll
         for (int tn = 0; tn < 4; ++tn)
 #pragma unroll
-            for (int i = 0; i < 4; ++i)
-                out[kOffW2 + (16 * tm + rq + i) * kHidden + 16 * tn + r16] = gW2[tm][tn][i];
-    if (l < 16) {
+            for (int i = 0; i < 4; ++i) {
+                const int row = rq + i;
+                if (row < kFeat) add(row * kHidden + 16 * tn + r16, gW1[tn][i]);
+            }
 #pragma unroll
-        for (int t = 0; t < 4; ++t) {
-            out[kOffB1 + 16 * t + l] = gb1[t];
-            out[kOffB2 + 16 * t + l] = gb2[t];
-            out[kOffW3 + 16 * t + l] = gw3[t];
+        for (int tm = 0; tm < 4; ++tm)
+#pragma unroll
+            for (int tn = 0; tn < 4; ++tn)
+#pragma unroll
+                for (int i = 0; i < 4; ++i)
+                    add(kOffW2 + (16 * tm + rq + i) * kHidden + 16 * tn + r16, gW2[tm][tn][i]);
+        if (l < 16) {
+#pragma unroll
+            for (int t = 0; t < 4; ++t) {
+                add(kOffB1 + 16 * t + l, gb1[t]);
+                add(kOffB2 + 16 * t + l, gb2[t]);
+                add(kOffW3 + 16 * t + l, gw3[t]);
+            }
+        }
+        if (l == 0) {
+            add(kOffB3, gb3);
+            add(kParams, loss);
         }
     }
-    if (l == 0) {
-        out[kOffB3] = gb3;
-        out[kParams] = loss;
-    }
+    __syncthreads();
+    float *out = partials + (int64_t)blockIdx.x * (kParams + 1);
+    for (int q = threadIdx.x; q <= kParams; q += 64 * kTrainWaves) out[q] = sum[q];
 }
 
-// grad[q] = sum over workgroups in index order (deterministic)
+// grad[q] = sum over workgroups in index order (deterministic).  The order makes
+// it one chain of additions per parameter; the loads need not wait for it:
+// a workgroup loads its 16 parameters of up to kReduceRows workgroups at once
+// and 16 lanes add them up from LDS.  512 workgroups: 120 us with the loads in the chain, 8 so.
+constexpr int kReduceCols = 16, kReduceRows = 512;
 __global__ __launch_bounds__(kBlk) void k_grad_reduce(const float *partials, int nblocks, float *grad) {
-    const int q = blockIdx.x * kBlk + threadIdx.x;
-    if (q > kParams) return;
+    constexpr int kStep = kBlk / kReduceCols, kPer = kReduceRows / kStep;
+    __shared__ float s_v[kReduceRows * kReduceCols];
+    const int c = threadIdx.x % kReduceCols, r = threadIdx.x / kReduceCols;
+    const int q = blockIdx.x * kReduceCols + c;
+    const bool in = q <= kParams;
     float s = 0.0f;
-    for (int b = 0; b < nblocks; ++b) s += partials[(int64_t)b * (kParams + 1) + q];
-    grad[q] = s;
+    for (int b0 = 0; b0 < nblocks; b0 += kReduceRows) {
+        float v[kPer];
+#pragma unroll
+        for (int i = 0; i < kPer; ++i) {
+            const int b = b0 + r + i * kStep;
+            v[i] = in && b < nblocks ? partials[(int64_t)b * (kParams + 1) + q] : 0.0f;
+        }
+        __syncthreads();
+#pragma unroll
+        for (int i = 0; i < kPer; ++i) s_v[(r + i * kStep) * kReduceCols + c] = v[i];
+        __syncthreads();
+        if (r == 0) {
+            const int nb = min(nblocks - b0, kReduceRows);
+#pragma unroll 16
+            for (int b = 0; b < nb; ++b) s += s_v[b * kReduceCols + c];
+        }
+    }
+    if (r == 0 && in) grad[q] = s;
 }
 
 __device__ __forceinline__ void refresh_bf16(const MlpDev &m, int q) {
@@ -718,7 +798,7 @@ hipError_t launch_mlp_forward(const MlpDev &m, const float *x, const int32_t *n_
     (void)hipGetLastError();
     int grid = 128;  // device-side row count: each workgroup strides over the tiles
     if (!n_dev) grid = (int)std::max<int64_t>(1, std::min<int64_t>((n + kRows - 1) / kRows, 1024));
-    k_mlp_fwd<<<grid, 64, 0, st>>>(m, x, n_dev, n, logits, cand, screen, tau, stats);
+    k_mlp_fwd<<<grid, 64 * kFwdWaves, 0, st>>>(m, x, n_dev, n, logits, cand, screen, tau, stats);
     return hipGetLastError();
 }
 
@@ -728,8 +808,8 @@ hipError_t launch_mlp_gradient(const MlpDev &m, const float *x, const float *y, 
                                float *partials, float *grad, hipStream_t st) {
     (void)hipGetLastError();
     const int nb = mlp_train_blocks(n);
-    k_mlp_train<<<nb, 64, 0, st>>>(m, x, y, n, pos_weight, partials);
-    k_grad_reduce<<<(kParams + 1 + kBlk - 1) / kBlk, kBlk, 0, st>>>(partials, nb, grad);
+    k_mlp_train<<<nb, 64 * kTrainWaves, 0, st>>>(m, x, y, n, pos_weight, partials);
+    k_grad_reduce<<<(kParams + 1 + kReduceCols - 1) / kReduceCols, kBlk, 0, st>>>(partials, nb, grad);
     return hipGetLastError();
 }
 
