@@ -802,7 +802,14 @@ hipError_t launch_mlp_forward(const MlpDev &m, const float *x, const int32_t *n_
     return hipGetLastError();
 }
 
-int mlp_train_blocks(int64_t n) { return (int)std::max<int64_t>(1, std::min<int64_t>((n + kRows - 1) / kRows, 512)); }
+// Workgroups of a gradient over n rows (the partial sums are allocated for the
+// most there can be: n = INT64_MAX).
+static constexpr int train_blocks(int64_t n) {
+    return n >= (int64_t)512 * kRows ? 512 : n <= kRows ? 1 : (int)((n + kRows - 1) / kRows);
+}
+static_assert(train_blocks(INT64_MAX) == 512 && train_blocks(0) == 1 && train_blocks(33) == 2, "");
+
+int mlp_train_blocks(int64_t n) { return train_blocks(n); }
 
 hipError_t launch_mlp_gradient(const MlpDev &m, const float *x, const float *y, int64_t n, float pos_weight,
                                float *partials, float *grad, hipStream_t st) {
