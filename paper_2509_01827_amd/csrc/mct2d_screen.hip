@@ -301,21 +301,33 @@ __device__ __forceinline__ float gelu_erf(float z) { return erff(z * 0.707106781
 __device__ __forceinline__ __bf16 to_bf(float v) { return (__bf16)v; }
 __device__ __forceinline__ float from_bf(__bf16 v) { return (float)v; }
 
+// Every MFMA operand is eight consecutive k of one row or column, so each array
+// is kept with that index last (twice where both of its indices are summed
+// over) and read as one 16-byte load; the paddings (40, 72 elements a row)
+// spread a wavefront's rows over all LDS banks.
+constexpr int kPadR = kRows + 8, kPadH = kHidden + 8;
+static_assert(kHidden * 18 <= 16 * kPadH, "dZ1 of 16 rows over their dZ2");
+static_assert(kRows == kIn, "one padding for both");
+
 struct MlpShared {
-    alignas(16) __bf16 w1[kIn * kHidden];      // [k][n]
-    alignas(16) __bf16 w2[kHidden * kHidden];  // [m][n]
+    alignas(16) __bf16 w1t[kHidden * kPadR];  // [n][k]
+    alignas(16) __bf16 w2t[kHidden * kPadH];  // [n][m]
     __bf16 w3[kHidden];
     float b1[kHidden], b2[kHidden];
     float b3;
 };
+struct MlpTrainShared : MlpShared {
+    alignas(16) __bf16 w2[kHidden * kPadH];  // [m][n]
+};
 
 // One wavefront's rows.
 struct MlpTile {
-    alignas(16) __bf16 x[kRows * kIn];  // [row][k]
-    __bf16 h1[kRows * kHidden];         // [row][m]
+    alignas(16) __bf16 h1[kRows * kPadH];  // [row][m], then dZ2 [row][n], then dZ1
 };
 struct MlpTrainTile : MlpTile {
-    __bf16 dz[kRows * kHidden];  // dZ2, then dZ1 [row][n]
+    alignas(16) __bf16 h1t[kHidden * kPadR];  // [m][row]
+    alignas(16) __bf16 dzt[kHidden * kPadR];  // dZ2, then dZ1 [n][row]
+    alignas(16) __bf16 xt[16 * kPadR];        // [k][row]
 };
 
 // Orders a wavefront's accesses to its own tile: LDS serves a wavefront in
@@ -325,14 +337,26 @@ __device__ __forceinline__ void tile_sync() {
     __builtin_amdgcn_wave_barrier();
 }
 
-__device__ void load_weights(const MlpDev &m, MlpShared &sh) {
-    // 16-byte copies (8 bfloat16 each); the arrays are 256-byte aligned
-    const uint4 *w1 = reinterpret_cast<const uint4 *>(m.w1b);
-    const uint4 *w2 = reinterpret_cast<const uint4 *>(m.w2b);
-    uint4 *s1 = reinterpret_cast<uint4 *>(sh.w1);
-    uint4 *s2 = reinterpret_cast<uint4 *>(sh.w2);
-    for (int i = threadIdx.x; i < kIn * kHidden / 8; i += blockDim.x) s1[i] = w1[i];
-    for (int i = threadIdx.x; i < kHidden * kHidden / 8; i += blockDim.x) s2[i] = w2[i];
+typedef __bf16 bf16x4 __attribute__((ext_vector_type(4)));
+
+template <bool GRAD, class SH>
+__device__ __forceinline__ void load_weights(const MlpDev &m, SH &sh) {
+    // 16-byte loads (8 bfloat16 of a row each); the arrays are 256-byte aligned
+    const bf16x8 *w1 = reinterpret_cast<const bf16x8 *>(m.w1b);
+    const bf16x8 *w2 = reinterpret_cast<const bf16x8 *>(m.w2b);
+    for (int i = threadIdx.x; i < kIn * kHidden / 8; i += blockDim.x) {
+        const int k = i / (kHidden / 8), n = 8 * (i % (kHidden / 8));
+        const bf16x8 v = w1[i];
+#pragma unroll
+        for (int j = 0; j < 8; ++j) sh.w1t[(n + j) * kPadR + k] = v[j];
+    }
+    for (int i = threadIdx.x; i < kHidden * kHidden / 8; i += blockDim.x) {
+        const int k = i / (kHidden / 8), n = 8 * (i % (kHidden / 8));
+        const bf16x8 v = w2[i];
+#pragma unroll
+        for (int j = 0; j < 8; ++j) sh.w2t[(n + j) * kPadH + k] = v[j];
+        if constexpr (GRAD) *reinterpret_cast<bf16x8 *>(&sh.w2[k * kPadH + n]) = v;
+    }
     const __bf16 *w3 = reinterpret_cast<const __bf16 *>(m.w3b);
     for (int i = threadIdx.x; i < kHidden; i += blockDim.x) {
         sh.w3[i] = w3[i];
@@ -342,93 +366,90 @@ __device__ void load_weights(const MlpDev &m, MlpShared &sh) {
     if (threadIdx.x == 0) sh.b3 = m.master[kOffB3];
 }
 
-__device__ void load_rows(const float *X, int64_t r0, int64_t n, MlpTile &tl) {
-    for (int i = threadIdx.x & 63; i < kRows * kIn; i += 64) {
-        const int r = i / kIn, k = i % kIn;
-        float v = 0.0f;
-        if (k < kFeat && r0 + r < n) v = X[(r0 + r) * kFeat + k];
-        tl.x[i] = to_bf(v);
+__device__ __forceinline__ bf16x8 frag(const __bf16 *p) { return *reinterpret_cast<const bf16x8 *>(p); }
+
+// Input operand of the 16 rows from r0: lane l holds k = 8 (l >> 4) + i of row
+// l & 15 (kFeat values a row, zero beyond them and beyond the last row).
+__device__ __forceinline__ bf16x8 load_rows(const float *X, int64_t r0, int64_t n, int l) {
+    const int r16 = l & 15, kq = 8 * (l >> 4);
+    bf16x8 v;
+#pragma unroll
+    for (int i = 0; i < 8; ++i) {
+        float f = 0.0f;
+        if (kq + i < kFeat && r0 + r16 < n) f = X[(r0 + r16) * kFeat + kq + i];
+        v[i] = to_bf(f);
     }
+    return v;
 }
 
-// Forward pass of one 32-row tile.  Leaves h1 in LDS and returns in
-// registers the logit of this lane's rows (all 16 lanes of a row group hold
-// the sum) and, GRAD, the slopes of both GELU layers and the second hidden
-// layer (D layout).
+// Forward pass of 16 rows (half h of the tile) from their input operand.  Leaves
+// h1 in LDS and returns in registers the logit of this lane's rows (all 16 lanes
+// of a row group hold the sum) and, GRAD, the slopes of both GELU layers and the
+// second hidden layer (D layout).
 struct Fwd {
-    float d1[2][4][4], d2[2][4][4];
-    __bf16 h2[2][4][4];
-    float z3[2][4];
+    float d1[4][4], d2[4][4];
+    bf16x4 h2[4];
+    float z3[4];
 };
 
-template <bool GRAD>
-__device__ __forceinline__ void forward_tile(const MlpShared &sh, MlpTile &tl, Fwd &f) {
-    const int l = threadIdx.x & 63, r16 = l & 15, kq = 8 * (l >> 4), rq = 4 * (l >> 4);
+template <bool GRAD, class TL>
+__device__ __forceinline__ void forward_half(const MlpShared &sh, TL &tl, int h, bf16x8 x, int l, Fwd &f) {
+    const int r16 = l & 15, kq = 8 * (l >> 4), rq = 4 * (l >> 4);
     // layer 1
 #pragma unroll
-    for (int h = 0; h < 2; ++h) {
-        bf16x8 a;
+    for (int t = 0; t < 4; ++t) {
+        const bf16x8 b = frag(&sh.w1t[(16 * t + r16) * kPadR + kq]);
+        f32x4 acc = {0.0f, 0.0f, 0.0f, 0.0f};
+        acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(x, b, acc, 0, 0, 0);
+        bf16x4 hv;
 #pragma unroll
-        for (int i = 0; i < 8; ++i) a[i] = tl.x[(16 * h + r16) * kIn + kq + i];
-#pragma unroll
-        for (int t = 0; t < 4; ++t) {
-            bf16x8 b;
-#pragma unroll
-            for (int i = 0; i < 8; ++i) b[i] = sh.w1[(kq + i) * kHidden + 16 * t + r16];
-            f32x4 acc = {0.0f, 0.0f, 0.0f, 0.0f};
-            acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, b, acc, 0, 0, 0);
-#pragma unroll
-            for (int i = 0; i < 4; ++i) {
-                const float z = acc[i] + sh.b1[16 * t + r16];
-                const float e = gelu_erf(z);
-                if (GRAD) f.d1[h][t][i] = gelu_slope(z, e);
-                tl.h1[(16 * h + rq + i) * kHidden + 16 * t + r16] = to_bf(gelu(z, e));
-            }
+        for (int i = 0; i < 4; ++i) {
+            const float z = acc[i] + sh.b1[16 * t + r16];
+            const float e = gelu_erf(z);
+            if (GRAD) f.d1[t][i] = gelu_slope(z, e);
+            hv[i] = to_bf(gelu(z, e));
+            tl.h1[(16 * h + rq + i) * kPadH + 16 * t + r16] = hv[i];
         }
+        if constexpr (GRAD) *reinterpret_cast<bf16x4 *>(&tl.h1t[(16 * t + r16) * kPadR + 16 * h + rq]) = hv;
     }
     tile_sync();
     // layer 2 and the output layer
+    bf16x8 a[2];
 #pragma unroll
-    for (int h = 0; h < 2; ++h) {
-        float part[4] = {0.0f, 0.0f, 0.0f, 0.0f};
+    for (int kc = 0; kc < 2; ++kc) a[kc] = frag(&tl.h1[(16 * h + r16) * kPadH + 32 * kc + kq]);
+    float part[4] = {0.0f, 0.0f, 0.0f, 0.0f};
 #pragma unroll
-        for (int t = 0; t < 4; ++t) {
-            f32x4 acc = {0.0f, 0.0f, 0.0f, 0.0f};
+    for (int t = 0; t < 4; ++t) {
+        f32x4 acc = {0.0f, 0.0f, 0.0f, 0.0f};
 #pragma unroll
-            for (int kc = 0; kc < 2; ++kc) {
-                bf16x8 a, b;
-#pragma unroll
-                for (int i = 0; i < 8; ++i) {
-                    a[i] = tl.h1[(16 * h + r16) * kHidden + 32 * kc + kq + i];
-                    b[i] = sh.w2[(32 * kc + kq + i) * kHidden + 16 * t + r16];
-                }
-                acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, b, acc, 0, 0, 0);
-            }
-#pragma unroll
-            for (int i = 0; i < 4; ++i) {
-                const float z = acc[i] + sh.b2[16 * t + r16];
-                const float e = gelu_erf(z);
-                const __bf16 hv = to_bf(gelu(z, e));
-                if (GRAD) {
-                    f.d2[h][t][i] = gelu_slope(z, e);
-                    f.h2[h][t][i] = hv;
-                }
-                part[i] += from_bf(hv) * from_bf(sh.w3[16 * t + r16]);
-            }
+        for (int kc = 0; kc < 2; ++kc) {
+            const bf16x8 b = frag(&sh.w2t[(16 * t + r16) * kPadH + 32 * kc + kq]);
+            acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[kc], b, acc, 0, 0, 0);
         }
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
-            float v = part[i];
-#pragma unroll
-            for (int off = 1; off < 16; off <<= 1) v += __shfl_xor(v, off, 64);
-            f.z3[h][i] = v + sh.b3;
+            const float z = acc[i] + sh.b2[16 * t + r16];
+            const float e = gelu_erf(z);
+            const __bf16 hv = to_bf(gelu(z, e));
+            if (GRAD) {
+                f.d2[t][i] = gelu_slope(z, e);
+                f.h2[t][i] = hv;
+            }
+            part[i] += from_bf(hv) * from_bf(sh.w3[16 * t + r16]);
         }
+    }
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+        float v = part[i];
+#pragma unroll
+        for (int off = 1; off < 16; off <<= 1) v += __shfl_xor(v, off, 64);
+        f.z3[i] = v + sh.b3;
     }
 }
 
 // Four wavefronts per workgroup share the weights, each with its own tiles: one
 // tile is a chain of some 10 us, so four per SIMD are under way.  65 536 rows:
-// 29 us with one wavefront per workgroup, 19 with four.
+// 29 us with one wavefront per workgroup, 16 with four.
 constexpr int kFwdWaves = 4;
 __global__ __launch_bounds__(64 * kFwdWaves) void k_mlp_fwd(MlpDev m, const float *X, const int32_t *n_dev,
                                                             int64_t n_host, float *logits, const int32_t *cand,
@@ -436,7 +457,7 @@ __global__ __launch_bounds__(64 * kFwdWaves) void k_mlp_fwd(MlpDev m, const floa
     __shared__ MlpShared sh;
     __shared__ MlpTile s_tile[kFwdWaves];
     const int64_t n = n_dev ? (int64_t)*n_dev : n_host;
-    load_weights(m, sh);
+    load_weights<false>(m, sh);
     __syncthreads();
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     MlpTile &tl = s_tile[wave];
@@ -444,28 +465,26 @@ __global__ __launch_bounds__(64 * kFwdWaves) void k_mlp_fwd(MlpDev m, const floa
     uint8_t *bytes = reinterpret_cast<uint8_t *>(screen);
     for (int64_t r0 = ((int64_t)wave * gridDim.x + blockIdx.x) * kRows; r0 < n;
          r0 += (int64_t)kFwdWaves * gridDim.x * kRows) {
-        tile_sync();  // previous tile consumed
-        load_rows(X, r0, n, tl);
-        tile_sync();
-        Fwd f;
-        forward_tile<false>(sh, tl, f);
         int flagged = 0;
-        if (r16 == 0) {
+#pragma unroll 1
+        for (int h = 0; h < 2; ++h) {
+            Fwd f;
+            forward_half<false>(sh, tl, h, load_rows(X, r0 + 16 * h, n, l), l, f);
+            if (r16 != 0) continue;
 #pragma unroll
-            for (int h = 0; h < 2; ++h)
-#pragma unroll
-                for (int i = 0; i < 4; ++i) {
-                    const int64_t r = r0 + 16 * h + rq + i;
-                    if (r >= n) continue;
-                    const float z = f.z3[h][i];
-                    logits[r] = z;
-                    if (screen) {
-                        const bool flag = z > tau;
-                        bytes[cand[r]] = flag ? kScreenFlagged : kScreenSkip;
-                        flagged += flag;
-                    }
+            for (int i = 0; i < 4; ++i) {
+                const int64_t r = r0 + 16 * h + rq + i;
+                if (r >= n) continue;
+                const float z = f.z3[i];
+                logits[r] = z;
+                if (screen) {
+                    const bool flag = z > tau;
+                    bytes[cand[r]] = flag ? kScreenFlagged : kScreenSkip;
+                    flagged += flag;
                 }
+            }
         }
+        tile_sync();  // (the next tile overwrites h1)
         if (screen) {
 #pragma unroll
             for (int off = 16; off < 64; off <<= 1) flagged += __shfl_xor(flagged, off, 64);
@@ -477,26 +496,27 @@ __global__ __launch_bounds__(64 * kFwdWaves) void k_mlp_fwd(MlpDev m, const floa
 // Gradient of the mean weighted logistic loss, one partial per workgroup:
 // partials[b * (kParams + 1) + q], q = kParams is the loss.
 //
-// A tile of 32 rows is one long chain for its wavefront (LDS, MFMA and some 130
-// erf per lane, 25 us), so what counts is how many are under way: four
-// wavefronts per workgroup share the weights, each with its own rows, and add
-// their sums up in order at the end.  65 536 rows: 111 us with one wavefront per workgroup, 64 with four.
-constexpr int kTrainWaves = 4;
+// A tile of 32 rows is one long chain for its wavefront (some 130 exp and erf per
+// lane), so what counts is how many are under way: eight wavefronts per workgroup
+// share the weights, two per SIMD with their accumulators in registers, each
+// with its own rows; their sums are added up in order at the end.  65 536 rows:
+// 111 us with one wavefront per workgroup, operands gathered by 2-byte loads and
+// both halves of a tile at once; 33 us now.
+constexpr int kTrainWaves = 8;
 __global__ __launch_bounds__(64 * kTrainWaves) void k_mlp_train(MlpDev m, const float *X, const float *Y, int64_t n,
                                                                 float pos_weight, float *partials) {
     struct Work {
-        MlpShared sh;
+        MlpTrainShared sh;
         MlpTrainTile tile[kTrainWaves];
     };
-    constexpr size_t kSum = sizeof(float) * (kParams + 1);
-    __shared__ __attribute__((aligned(16))) char s_mem[sizeof(Work) > kSum ? sizeof(Work) : kSum];
+    __shared__ __attribute__((aligned(16))) char s_mem[sizeof(Work)];
     Work &wk = *reinterpret_cast<Work *>(s_mem);
-    MlpShared &sh = wk.sh;
-    load_weights(m, sh);
+    MlpTrainShared &sh = wk.sh;
+    load_weights<true>(m, sh);
     __syncthreads();
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     MlpTrainTile &tl = wk.tile[wave];
-    const int l = threadIdx.x & 63, r16 = l & 15, kq = 8 * (l >> 4), rq = 4 * (l >> 4);
+    const int lane = threadIdx.x & 63;
     const float inv_n = 1.0f / (float)n;
     f32x4 gW2[4][4], gW1[4];
 #pragma unroll
@@ -509,14 +529,23 @@ __global__ __launch_bounds__(64 * kTrainWaves) void k_mlp_train(MlpDev m, const 
     float gb3 = 0.0f, loss = 0.0f;
     for (int64_t r0 = ((int64_t)wave * gridDim.x + blockIdx.x) * kRows; r0 < n;
          r0 += (int64_t)kTrainWaves * gridDim.x * kRows) {
-        tile_sync();
-        load_rows(X, r0, n, tl);
-        tile_sync();
-        Fwd f;
-        forward_tile<true>(sh, tl, f);
-        // output layer and dZ2
+        // the lane's number anew in every tile: weights are read from LDS where they
+        // are used, not held in registers across the loop
+        int l = lane;
+        asm volatile("" : "+v"(l));
+        const int r16 = l & 15, kq = 8 * (l >> 4), rq = 4 * (l >> 4);
+#pragma unroll 1  // (both halves at once would fit neither the registers nor the instruction cache)
+        for (int h = 0; h < 2; ++h) {
+            Fwd f;
+            const bf16x8 x = load_rows(X, r0 + 16 * h, n, l);
+            if (kq < 16) {
 #pragma unroll
-        for (int h = 0; h < 2; ++h)
+                for (int i = 0; i < 8; ++i) tl.xt[(kq + i) * kPadR + 16 * h + r16] = x[i];
+            }
+            forward_half<true>(sh, tl, h, x, l, f);
+            tile_sync();
+            // output layer and dZ2 (over h1, which is no longer read)
+            bf16x4 dzv[4];
 #pragma unroll
             for (int i = 0; i < 4; ++i) {
                 const int64_t r = r0 + 16 * h + rq + i;
@@ -524,7 +553,7 @@ __global__ __launch_bounds__(64 * kTrainWaves) void k_mlp_train(MlpDev m, const 
                 if (r < n) {
                     const float y = Y[r];
                     const float w = (y > 0.5f) ? pos_weight : 1.0f;
-                    const float z = f.z3[h][i];
+                    const float z = f.z3[i];
                     const float sp = fmaxf(z, 0.0f) + log1pf(expf(-fabsf(z)));  // softplus
                     if (r16 == 0) loss += w * (sp - y * z) * inv_n;
                     dz3 = w * (1.0f / (1.0f + expf(-z)) - y) * inv_n;
@@ -533,75 +562,72 @@ __global__ __launch_bounds__(64 * kTrainWaves) void k_mlp_train(MlpDev m, const 
 #pragma unroll
                 for (int t = 0; t < 4; ++t) {
                     const int col = 16 * t + r16;
-                    gw3[t] += from_bf(f.h2[h][t][i]) * dz3;
+                    gw3[t] += from_bf(f.h2[t][i]) * dz3;
                     const float dh2 = dz3 * from_bf(sh.w3[col]);
-                    const __bf16 dz2 = to_bf(dh2 * f.d2[h][t][i]);
+                    const __bf16 dz2 = to_bf(dh2 * f.d2[t][i]);
                     gb2[t] += from_bf(dz2);
-                    tl.dz[(16 * h + rq + i) * kHidden + col] = dz2;
+                    tl.h1[(16 * h + rq + i) * kPadH + col] = dz2;
+                    dzv[t][i] = dz2;
                 }
             }
-        tile_sync();
-        // gW2 += H1^T dZ2 (K = the 32 rows of the tile)
 #pragma unroll
-        for (int tm = 0; tm < 4; ++tm) {
-            bf16x8 a;
+            for (int t = 0; t < 4; ++t)
+                *reinterpret_cast<bf16x4 *>(&tl.dzt[(16 * t + r16) * kPadR + 16 * h + rq]) = dzv[t];
+            tile_sync();
+            // dH1 = dZ2 W2^T, then dZ1, over this half's dZ2 rows (as [n][16 rows], 18
+            // apart) until the transposed dZ2 is no longer read
+            bf16x8 a[2];
 #pragma unroll
-            for (int i = 0; i < 8; ++i) a[i] = tl.h1[(kq + i) * kHidden + 16 * tm + r16];
-#pragma unroll
-            for (int tn = 0; tn < 4; ++tn) {
-                bf16x8 b;
-#pragma unroll
-                for (int i = 0; i < 8; ++i) b[i] = tl.dz[(kq + i) * kHidden + 16 * tn + r16];
-                gW2[tm][tn] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, b, gW2[tm][tn], 0, 0, 0);
-            }
-        }
-        // dH1 = dZ2 W2^T, then dZ1 (held until the dZ2 tile is no longer read)
-        __bf16 dz1v[2][4][4];
-#pragma unroll
-        for (int h = 0; h < 2; ++h)
+            for (int kc = 0; kc < 2; ++kc) a[kc] = frag(&tl.h1[(16 * h + r16) * kPadH + 32 * kc + kq]);
+            tile_sync();
 #pragma unroll
             for (int tm = 0; tm < 4; ++tm) {
                 f32x4 acc = {0.0f, 0.0f, 0.0f, 0.0f};
 #pragma unroll
                 for (int kc = 0; kc < 2; ++kc) {
-                    bf16x8 a, b;
-#pragma unroll
-                    for (int i = 0; i < 8; ++i) {
-                        a[i] = tl.dz[(16 * h + r16) * kHidden + 32 * kc + kq + i];
-                        b[i] = sh.w2[(16 * tm + r16) * kHidden + 32 * kc + kq + i];
-                    }
-                    acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, b, acc, 0, 0, 0);
+                    const bf16x8 b = frag(&sh.w2[(16 * tm + r16) * kPadH + 32 * kc + kq]);
+                    acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[kc], b, acc, 0, 0, 0);
                 }
 #pragma unroll
                 for (int i = 0; i < 4; ++i) {
-                    const __bf16 v = to_bf(acc[i] * f.d1[h][tm][i]);
-                    dz1v[h][tm][i] = v;
+                    const __bf16 v = to_bf(acc[i] * f.d1[tm][i]);
+                    tl.h1[16 * h * kPadH + (16 * tm + r16) * 18 + rq + i] = v;
                     gb1[tm] += from_bf(v);
                 }
             }
+        }
+        // gW2 += H1^T dZ2 (K = the 32 rows of the tile)
+        bf16x8 b[4];
+#pragma unroll
+        for (int tn = 0; tn < 4; ++tn) b[tn] = frag(&tl.dzt[(16 * tn + r16) * kPadR + kq]);
+#pragma unroll
+        for (int tm = 0; tm < 4; ++tm) {
+            const bf16x8 a = frag(&tl.h1t[(16 * tm + r16) * kPadR + kq]);
+#pragma unroll
+            for (int tn = 0; tn < 4; ++tn)
+                gW2[tm][tn] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, b[tn], gW2[tm][tn], 0, 0, 0);
+        }
         tile_sync();
 #pragma unroll
         for (int h = 0; h < 2; ++h)
 #pragma unroll
-            for (int tm = 0; tm < 4; ++tm)
+            for (int tm = 0; tm < 4; ++tm) {
+                bf16x4 v;
 #pragma unroll
-                for (int i = 0; i < 4; ++i) tl.dz[(16 * h + rq + i) * kHidden + 16 * tm + r16] = dz1v[h][tm][i];
+                for (int i = 0; i < 4; ++i) v[i] = tl.h1[16 * h * kPadH + (16 * tm + r16) * 18 + rq + i];
+                *reinterpret_cast<bf16x4 *>(&tl.dzt[(16 * tm + r16) * kPadR + 16 * h + rq]) = v;
+            }
         tile_sync();
         // gW1 += X^T dZ1 (input rows padded to 16)
-        {
-            bf16x8 a;
+        const bf16x8 xa = frag(&tl.xt[r16 * kPadR + kq]);
 #pragma unroll
-            for (int i = 0; i < 8; ++i) a[i] = tl.x[(kq + i) * kIn + r16];
-#pragma unroll
-            for (int tn = 0; tn < 4; ++tn) {
-                bf16x8 b;
-#pragma unroll
-                for (int i = 0; i < 8; ++i) b[i] = tl.dz[(kq + i) * kHidden + 16 * tn + r16];
-                gW1[tn] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, b, gW1[tn], 0, 0, 0);
-            }
-        }
+        for (int tn = 0; tn < 4; ++tn)
+            gW1[tn] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(xa, frag(&tl.dzt[(16 * tn + r16) * kPadR + kq]), gW1[tn],
+                                                              0, 0, 0);
+        tile_sync();
     }
     // column sums over the four row groups of the wavefront
+    const int l = lane;
 #pragma unroll
     for (int t = 0; t < 4; ++t) {
         gb1[t] += __shfl_xor(gb1[t], 16, 64);
@@ -616,48 +642,58 @@ __global__ __launch_bounds__(64 * kTrainWaves) void k_mlp_train(MlpDev m, const 
         gb3 += __shfl_xor(gb3, off, 64);
         loss += __shfl_xor(loss, off, 64);
     }
-    // the wavefronts' sums, in order
-    float *const sum = reinterpret_cast<float *>(s_mem);
-    for (int w = 0; w < kTrainWaves; ++w) {
+    // the wavefronts' sums, 16 values per lane at a time through LDS: value v of
+    // lane l at 64 v + l, a plane of them per wavefront; added in their order
+    float *const plane = reinterpret_cast<float *>(s_mem);
+    constexpr int kPlane = 16 * 64;
+    static_assert(sizeof(float) * kPlane * kTrainWaves <= sizeof(s_mem), "the planes of all wavefronts");
+    float *const out = partials + (int64_t)blockIdx.x * (kParams + 1);
+    auto combine = [&](const float (&v)[16], auto &&place) {
         __syncthreads();
-        if (w != wave) continue;
-        auto add = [&](int q, float v) { sum[q] = w == 0 ? v : sum[q] + v; };
 #pragma unroll
-        for (int tn = 0; tn < 4; ++tn)
+        for (int i = 0; i < 16; ++i) plane[wave * kPlane + 64 * i + l] = v[i];
+        __syncthreads();
+        for (int j = threadIdx.x; j < kPlane; j += 64 * kTrainWaves) {
+            const int q = place(j >> 6, j & 63);
+            if (q < 0) continue;
+            float t = plane[j];
 #pragma unroll
-            for (int i = 0; i < 4; ++i) {
-                const int row = rq + i;
-                if (row < kFeat) add(row * kHidden + 16 * tn + r16, gW1[tn][i]);
-            }
-#pragma unroll
-        for (int tm = 0; tm < 4; ++tm)
-#pragma unroll
-            for (int tn = 0; tn < 4; ++tn)
-#pragma unroll
-                for (int i = 0; i < 4; ++i)
-                    add(kOffW2 + (16 * tm + rq + i) * kHidden + 16 * tn + r16, gW2[tm][tn][i]);
-        if (l < 16) {
-#pragma unroll
-            for (int t = 0; t < 4; ++t) {
-                add(kOffB1 + 16 * t + l, gb1[t]);
-                add(kOffB2 + 16 * t + l, gb2[t]);
-                add(kOffW3 + 16 * t + l, gw3[t]);
-            }
+            for (int w = 1; w < kTrainWaves; ++w) t += plane[w * kPlane + j];
+            out[q] = t;
         }
-        if (l == 0) {
-            add(kOffB3, gb3);
-            add(kParams, loss);
-        }
+    };
+    float v[16];
+#pragma unroll
+    for (int tm = 0; tm < 4; ++tm) {
+#pragma unroll
+        for (int i = 0; i < 16; ++i) v[i] = gW2[tm][i >> 2][i & 3];
+        combine(v, [&](int i, int lane_) {
+            return kOffW2 + (16 * tm + 4 * (lane_ >> 4) + (i & 3)) * kHidden + 16 * (i >> 2) + (lane_ & 15);
+        });
     }
-    __syncthreads();
-    float *out = partials + (int64_t)blockIdx.x * (kParams + 1);
-    for (int q = threadIdx.x; q <= kParams; q += 64 * kTrainWaves) out[q] = sum[q];
+#pragma unroll
+    for (int i = 0; i < 16; ++i) v[i] = gW1[i >> 2][i & 3];
+    combine(v, [&](int i, int lane_) {
+        const int row = 4 * (lane_ >> 4) + (i & 3);
+        return row < kFeat ? row * kHidden + 16 * (i >> 2) + (lane_ & 15) : -1;
+    });
+#pragma unroll
+    for (int t = 0; t < 4; ++t) {
+        v[t] = gb1[t];
+        v[4 + t] = gb2[t];
+        v[8 + t] = gw3[t];
+        v[12 + t] = t == 0 ? gb3 : t == 1 ? loss : 0.0f;
+    }
+    combine(v, [&](int i, int lane_) {
+        if (i < 12) return lane_ < 16 ? (i < 4 ? kOffB1 : i < 8 ? kOffB2 : kOffW3) + 16 * (i & 3) + lane_ : -1;
+        return lane_ == 0 && i < 14 ? (i == 12 ? kOffB3 : kParams) : -1;
+    });
 }
 
 // grad[q] = sum over workgroups in index order (deterministic).  The order makes
 // it one chain of additions per parameter; the loads need not wait for it:
 // a workgroup loads its 16 parameters of up to kReduceRows workgroups at once
-// and 16 lanes add them up from LDS.  512 workgroups: 120 us with the loads in the chain, 8 so.
+// and 16 lanes add them up from LDS.  512 workgroups: 120 us with the loads in the chain, 8 so; 256 now, 5.
 constexpr int kReduceCols = 16, kReduceRows = 512;
 __global__ __launch_bounds__(kBlk) void k_grad_reduce(const float *partials, int nblocks, float *grad) {
     constexpr int kStep = kBlk / kReduceCols, kPer = kReduceRows / kStep;
@@ -797,7 +833,7 @@ hipError_t launch_mlp_forward(const MlpDev &m, const float *x, const int32_t *n_
                               hipStream_t st) {
     (void)hipGetLastError();
     int grid = 128;  // device-side row count: each workgroup strides over the tiles
-    if (!n_dev) grid = (int)std::max<int64_t>(1, std::min<int64_t>((n + kRows - 1) / kRows, 1024));
+    if (!n_dev) grid = (int)std::max<int64_t>(1, std::min<int64_t>((n + kRows - 1) / kRows, 512));
     k_mlp_fwd<<<grid, 64 * kFwdWaves, 0, st>>>(m, x, n_dev, n, logits, cand, screen, tau, stats);
     return hipGetLastError();
 }
@@ -805,9 +841,9 @@ hipError_t launch_mlp_forward(const MlpDev &m, const float *x, const int32_t *n_
 // Workgroups of a gradient over n rows (the partial sums are allocated for the
 // most there can be: n = INT64_MAX).
 static constexpr int train_blocks(int64_t n) {
-    return n >= (int64_t)512 * kRows ? 512 : n <= kRows ? 1 : (int)((n + kRows - 1) / kRows);
+    return n >= (int64_t)256 * kRows ? 256 : n <= kRows ? 1 : (int)((n + kRows - 1) / kRows);
 }
-static_assert(train_blocks(INT64_MAX) == 512 && train_blocks(0) == 1 && train_blocks(33) == 2, "");
+static_assert(train_blocks(INT64_MAX) == 256 && train_blocks(0) == 1 && train_blocks(33) == 2, "");
 
 int mlp_train_blocks(int64_t n) { return train_blocks(n); }
 
