@@ -95,8 +95,8 @@ TRI_SOURCES = ("mct2d_resident_mesh.hip", "mct2d_resident_mesh_host.cpp", "mct2d
                "mct2d_tri.h", "mct2d_device.h", "mct2d_impl.h")
 MEASURED_TRAFFIC = {
     # the batched lattice step kernel over the timed window (profiles/k_step_batch256_hbm_traffic.md)
-    "batch256": {"sources": Q4_SOURCES, "sha256": "2d97f53763b48eab505aea9b89981113f334cd680da2a90911d3cdc5243f47e7",
-                 "tile": 1, "fetch_kib": 286603.1083984375, "write_kib": 407268.94677734375},
+    "batch256": {"sources": Q4_SOURCES, "sha256": "b92d59fe58c87bbc741d175015493ce330a02686b64536d240f9e307c8e3b9e1",
+                 "tile": 1, "fetch_kib": 286587.1904296875, "write_kib": 411315.05712890625},
     # the resident mesh step, per step of a launch of 512 (profiles/k_mesh_resident.md)
     "tri320k": {"sources": TRI_SOURCES, "sha256": "af99620d799430c425ebe5cb5069ace69fafa017ecb89f289621803ee1ddf77c",
                 "tile": 5, "fetch_kib": 1158.0, "write_kib": 1160.1},

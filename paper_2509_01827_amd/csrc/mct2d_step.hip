@@ -158,6 +158,26 @@ __host__ __device__ constexpr bool lat_nzy(int k, int n) {
     return (k == 0 || k == 2) ? true : (k == 1 ? (n == 1 || n == 2) : (n == 0 || n == 3));
 }
 
+// The gradients that do not vanish take four values and their signs (the lattice
+// check compares them): dN/dx of an edge's own ends at edges 0 and 2 and of every
+// node at edges 1 and 3, dN/dy the other way round.  Read as four values, equal
+// products are formed once.
+struct LatGrad {
+    double ax, ay, hx, hy;
+};
+template <class LC>
+__host__ __device__ __forceinline__ LatGrad lat_grad(const LC *L) {
+    return LatGrad{L->B[0][1], L->B[1][6], L->B[1][1], L->B[0][6]};
+}
+__host__ __device__ __forceinline__ double lat_bx(const LatGrad &g, int k, int n) {
+    const double v = (k & 1) ? g.hx : g.ax;
+    return n == 1 || n == 2 ? v : -v;
+}
+__host__ __device__ __forceinline__ double lat_by(const LatGrad &g, int k, int n) {
+    const double v = (k & 1) ? g.ay : g.hy;
+    return n >= 2 ? v : -v;
+}
+
 // Strain (B u) at the midpoint of local edge K of a lattice element with
 // the shared gradients B: the terms of strain<4> in the same order, the
 // vanishing products left out (adding a zero product changes at most the
@@ -166,9 +186,10 @@ template <int K>
 __device__ __forceinline__ void strain_lat(const LatticeConst *L, const double ux[4], const double uy[4],
                                            double q[3]) {
     double exx = 0.0, eyy = 0.0, gxy = 0.0;
+    const LatGrad g = lat_grad(kconst(L));
 #pragma unroll
     for (int n = 0; n < 4; ++n) {
-        const double bx = kconst(L)->B[K][n], by = kconst(L)->B[K][4 + n];
+        const double bx = lat_bx(g, K, n), by = lat_by(g, K, n);
         if (lat_nzx(K, n)) exx = fma(bx, ux[n], exx);
         if (lat_nzy(K, n)) eyy = fma(by, uy[n], eyy);
         if (lat_nzy(K, n)) gxy = fma(by, ux[n], gxy);
@@ -360,9 +381,16 @@ __device__ __forceinline__ int32_t tip_after(const StepParamsT<T> &p, const Cand
 // of the pick over the whole GPU its tip point goes into the table.  The
 // NEAR instances carry the same code (the near log and the per-front pick
 // may be on together).
+//
+// The lattice instances are bound by instruction issue (the state's bytes take
+// half their time): the four shared gradient values in place of 24 constants
+// took the batched one from 345 to about 333 us per step (256 specimens, 13 M
+// nodes) and 2000 x 1000 elements from 54.6 to 52.7; the seventh workgroup per
+// compute unit (72 registers, 23 KB of LDS) the batch to 313.  The plain instance
+// spills at seven and gains nothing.
 template <class T, int TXE, int TYE, bool BATCHED, bool SC = false, bool UNI = false, bool NEAR = false,
           bool FRONT = false>
-__global__ __launch_bounds__(TXE *TYE, UNI ? 6 : 4) void k_step(StepParamsT<T> p0,
+__global__ __launch_bounds__(TXE *TYE, UNI ? (BATCHED && TXE == 16 ? 7 : 6) : 4) void k_step(StepParamsT<T> p0,
                                                                const StepParamsT<T> *__restrict__ views,
                                                                const int2 *__restrict__ units, int k_rel, int par0) {
     static_assert(!UNI || (sizeof(T) == 8 && !SC), "the lattice kernel is binary64 with the point rule");
@@ -838,6 +866,7 @@ __global__ __launch_bounds__(TXE *TYE, UNI ? 6 : 4) void k_step(StepParamsT<T> p
         // the general loop below with the shared gradients; a vanishing
         // gradient leaves one product of each pair
         T sx[4], sy[4];
+        const LatGrad g = lat_grad(kconst(p.lat));
 #pragma unroll
         for (int k = 0; k < 4; ++k) {
             T sg[3];
@@ -845,7 +874,7 @@ __global__ __launch_bounds__(TXE *TYE, UNI ? 6 : 4) void k_step(StepParamsT<T> p
             const T s0 = sg[0], s1 = sg[1], s2 = sg[2];
 #pragma unroll
             for (int n = 0; n < 4; ++n) {
-                const T bx = kconst(p.lat)->B[k][n], by = kconst(p.lat)->B[k][4 + n];
+                const T bx = lat_bx(g, k, n), by = lat_by(g, k, n);
                 T tx, ty;
                 if (lat_nzx(k, n) && lat_nzy(k, n)) {
                     tx = fmat(by, s2, bx * s0);
@@ -1459,6 +1488,13 @@ __global__ void k_lattice_ref(StepParams p, LatticeConst *ref, uint32_t *flag) {
         for (int n = 0; n < 4; ++n) {
             if (!lat_nzx(k, n) && L.B[k][n] != 0.0) f |= 2u;
             if (!lat_nzy(k, n) && L.B[k][4 + n] != 0.0) f |= 2u;
+        }
+    // the four values and their signs
+    const LatGrad g = lat_grad(&L);
+    for (int k = 0; k < 4; ++k)
+        for (int n = 0; n < 4; ++n) {
+            if (lat_nzx(k, n) && L.B[k][n] != lat_bx(g, k, n)) f |= 2u;
+            if (lat_nzy(k, n) && L.B[k][4 + n] != lat_by(g, k, n)) f |= 2u;
         }
     *flag = f;
 }
