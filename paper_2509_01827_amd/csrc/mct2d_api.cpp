@@ -2166,6 +2166,7 @@ int mct_restore(mct_ctx *c, const void *buf, int64_t bytes) {
         if (rc) return rc;
     }
     HIP_TRY(c, hipStreamSynchronize(c->stream));
+    HIP_TRY(c, hipMemsetAsync(c->dctl + S, 0, 16, c->stream));  // a resident launch's error
     for (int s = 0; s < S; ++s) {
         const Spec &sp = c->specs[s];
         p += 16 + sizeof(Control);

@@ -27,9 +27,10 @@ constexpr int kTagBits = 21;
 constexpr int kDataBits = 64 - kTagBits;
 constexpr uint32_t kTagMask = (1u << kTagBits) - 1u;
 constexpr uint64_t kDataMask = (1ull << kDataBits) - 1ull;
-// polls before a reader gives up (seconds; the launch is cooperative, so
-// every workgroup is resident and a word arrives within microseconds)
-constexpr int kSpinLimit = 1 << 22;
+// polls before a reader gives up (some half a minute; the launch is cooperative,
+// so a word arrives within microseconds unless kernels of other streams hold
+// compute units that this launch still waits for)
+constexpr int kSpinLimit = 1 << 25;
 constexpr int kBackoff = 4;  // pause after a vain poll, in 64 cycles
 
 __device__ __forceinline__ uint64_t word(uint32_t epoch, uint64_t data) {

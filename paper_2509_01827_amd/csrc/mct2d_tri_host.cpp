@@ -1345,6 +1345,7 @@ int restore(Model &m, Host h, const void *buf, int64_t bytes) {
     p += 24 + sizeof c;
     TRY(h, hipStreamSynchronize(h.stream));
     TRY(h, hipMemcpy(m.dctl, &c, sizeof c, hipMemcpyHostToDevice));
+    TRY(h, hipMemset(m.dctl + 1, 0, 8));  // a resident launch's error
     if (m.dfold_n) TRY(h, hipMemset(m.dfold_n, 0, 3 * sizeof(int32_t)));
     if (m.dfgrid) {
         TRY(h, front_grid_reset(m.dfgrid, h.stream));
