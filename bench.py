@@ -98,10 +98,10 @@ MEASURED_TRAFFIC = {
     "batch256": {"sources": Q4_SOURCES, "sha256": "b92d59fe58c87bbc741d175015493ce330a02686b64536d240f9e307c8e3b9e1",
                  "tile": 1, "fetch_kib": 286587.1904296875, "write_kib": 411315.05712890625},
     # the resident mesh step, per step of a launch of 512 (profiles/k_mesh_resident.md)
-    "tri320k": {"sources": TRI_SOURCES, "sha256": "a1777bf101c540c6e728b18d8a17c717089b57b5433d8f875e35f17021848ce6",
-                "tile": 5, "fetch_kib": 1158.0, "write_kib": 1160.1},
-    "quad160k": {"sources": TRI_SOURCES, "sha256": "a1777bf101c540c6e728b18d8a17c717089b57b5433d8f875e35f17021848ce6",
-                 "tile": 5, "fetch_kib": 1398.9, "write_kib": 1363.8},
+    "tri320k": {"sources": TRI_SOURCES, "sha256": "b9d3444662e9d50705ce4e2a1fbf8539fc8b1f06cb735cc0f674cfa44ad06278",
+                "tile": 5, "fetch_kib": 1133.5, "write_kib": 1160.1},
+    "quad160k": {"sources": TRI_SOURCES, "sha256": "b9d3444662e9d50705ce4e2a1fbf8539fc8b1f06cb735cc0f674cfa44ad06278",
+                 "tile": 5, "fetch_kib": 1376.5, "write_kib": 1363.8},
 }
 FETCH_SCALE, WRITE_SCALE = 262144.0 / 131086.604, 262144.0 / 262144.0
 

@@ -17,8 +17,8 @@
 // cycles, smoothing and forces 4500, candidates 2500, sums 2200, the exchange
 // 2500 to 4000), hence also the strides of the LDS arrays, at which the
 // wavefronts' accesses share no banks.  Per step, before -> after: 320 000
-// triangles 16.2 -> 7.1 us, 160 000 quadrilaterals 21 -> 7.8, 54 000 triangles
-// with cracks running 11 -> 6.3.
+// triangles 16.2 -> 6.7 us, 160 000 quadrilaterals 21 -> 7.7, 54 000 triangles
+// with cracks running 11 -> 6.0.
 //
 // A step, with four barriers (five on quadrilaterals):
 //   - the pick of the step before acts on the codes; every element of the patch
@@ -915,8 +915,14 @@ __global__ __launch_bounds__(NT) void k_mesh_resident(const MeshArgs A) {
                 a->p.v[g] = n_v;
             }
         }
-        // (the first poll waits: see k_resident)
-        for (int w = 0; w < nwg / 48; ++w) __builtin_amdgcn_s_sleep(4);
+        // As in k_resident the first poll waits, here twice as long: by measurement.
+        // us per step at nwg / 48, 32, 24, 16, 12 (plates of nx by
+        // 0.4 nx cells): 320 000 triangles 7.1, 6.8, 6.7, 7.3, 7.8; 53 000 on the
+        // cylinder 6.3, 6.1, 6.0, 6.1, 6.5; triangles at nx = 400 5.4, 4.7, 4.7,
+        // 5.3, 5.8, at 250 4.6, 4.5, 4.1, 4.1, 4.5; quadrilaterals at 258 7.8, 7.7,
+        // 7.7, 8.3, 8.9; below 24 patches none waits.  It is the slots' wait that
+        // counts: the longer one for the other patches' nodes alone changes nothing.
+        for (int w = 0; w < nwg / 24; ++w) __builtin_amdgcn_s_sleep(4);
         if (picks) {
             if (!last || b == 0) take_slots(ep + 1, base + s, NT - 1 - tid);
         } else if (!last) {
