@@ -153,7 +153,7 @@ __global__ __launch_bounds__(NT) void k_mesh_resident(const MeshArgs A) {
         asm volatile("" : "+s"(q));
         return q;
     };
-    __shared__ int s_ncand, s_ncel, s_ncorner, s_nthru, s_nred, s_ninl, s_stop, s_narr, s_npicks, s_pick, s_pcode, s_hit, s_nbc;
+    __shared__ int s_ncand, s_ncel, s_ncorner, s_nthru, s_nred, s_ninl, s_stop, s_narr, s_npicks, s_pick, s_pcode, s_hit, s_full, s_nbc;
     __shared__ Best<double> s_red[NW], s_inl[NW * EPT], s_pk[kPickWaves];
     __shared__ double s_phi, s_cv[4];
     __shared__ int2 s_picks[kMeshResidentSteps];
@@ -474,6 +474,9 @@ __global__ __launch_bounds__(NT) void k_mesh_resident(const MeshArgs A) {
             mat.E = q->p.E;
         }
         // ---- the pick of the step before ----------------------------------------
+        // (whether the candidates' lists are full is decided here, where nothing is
+        // added to them: behind the barrier some wavefronts list while others have
+        // still to look)
         if (const int pick = s_pick; pick >= 0) {  // uniform
             const uint8_t pc = (uint8_t)s_pcode;
 #pragma unroll
@@ -484,10 +487,12 @@ __global__ __launch_bounds__(NT) void k_mesh_resident(const MeshArgs A) {
                     s_code[slot] = pc;
                     list_split(el[r], slot);
                     s_hit = s;
+                    s_full = s_ncel > NCE;
                 }
             if (NV == 4 && ro < P.nredge && (int)s_rt[ro].w == pick) {
                 s_code[NE + ro] = pc;
                 s_hit = s;
+                s_full = s_ncel > NCE;
             }
         }
         // ---- strains ------------------------------------------------------------
@@ -543,9 +548,8 @@ __global__ __launch_bounds__(NT) void k_mesh_resident(const MeshArgs A) {
         }
         __syncthreads();
         if (s_hit == s) {  // uniform: an element of the patch or its ring split
-            const bool full = s_ncel > NCE;  // start the lists again, without the entries of split elements
+            const bool full = s_full != 0;  // start the lists again, without the entries of split elements
             if (full) {
-                __syncthreads();
                 if (tid == 0) s_ncel = s_ncand = 0;
                 ncached = 0;
                 __syncthreads();
