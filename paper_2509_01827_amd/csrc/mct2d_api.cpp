@@ -928,23 +928,28 @@ int upload(mct_ctx *c, T *&dst, const std::vector<T> &src) {
     return MCT_OK;
 }
 
-// The control block of specimen s; with the resident step also its error
-// word, which lies behind the block.
-int read_control(mct_ctx *c, int s, Control *h) {
-    struct {
-        Control ctl;
-        uint32_t err[4];
-    } v;
-    const bool res = c->res.threads != 0;
-    const mct::Fetch::Part part{c->dctl + s, res ? sizeof v : sizeof(Control)};
-    HIP_TRY(c, c->fetch.run(c->stream, &part, 1, &v, sizeof v, [&](int, size_t off, const char *d, size_t n) {
-        std::memcpy(reinterpret_cast<char *>(&v) + off, d, n);
-    }));
-    *h = v.ctl;
-    if (res && v.err[0])
-        return fail(c, MCT_EDEVICE, "resident step: a workgroup did not answer (step %lld)", (long long)v.ctl.base);
-    return MCT_OK;
+// What lies behind the control blocks: the resident step's error word.
+struct ResidentError {
+    uint32_t word[4];
+};
+
+int resident_failed(mct_ctx *c) {
+    return fail(c, MCT_EDEVICE, "resident step: a workgroup did not answer (the state is undefined until mct_restore)");
 }
+
+// A piece of device memory behind the work enqueued, or the resident step's error.
+int fetch_checked(mct_ctx *c, void *out, const void *src, size_t bytes) {
+    ResidentError err{};
+    const mct::Fetch::Part parts[2] = {{c->dctl + c->specs.size(), sizeof err}, {src, bytes}};
+    char *const to[2] = {reinterpret_cast<char *>(&err), static_cast<char *>(out)};
+    HIP_TRY(c, c->fetch.run(c->stream, parts, 2, out, bytes, [&](int i, size_t off, const char *d, size_t n) {
+        std::memcpy(to[i] + off, d, n);
+    }));
+    return err.word[0] ? resident_failed(c) : MCT_OK;
+}
+
+// The control block of specimen s.
+int read_control(mct_ctx *c, int s, Control *h) { return fetch_checked(c, h, c->dctl + s, sizeof *h); }
 
 }  // namespace
 
@@ -1757,12 +1762,8 @@ int mct_sync(mct_ctx *c) {
         if ((rc = widen_state(c))) return rc;
         HIP_TRY(c, hipMemsetAsync(c->dflag, 0, sizeof(int32_t), c->stream));
         HIP_TRY(c, mct::launch_check_finite(c->dux[par], c->duy[par], c->dvx, c->dvy, nn, c->dflag, c->stream));
-        HIP_TRY(c, hipMemcpyAsync(&flag, c->dflag, sizeof flag, hipMemcpyDeviceToHost, c->stream));
+        if ((rc = fetch_checked(c, &flag, c->dflag, sizeof flag))) return rc;
         HIP_TRY(c, hipStreamSynchronize(c->stream));
-        if (c->res.threads) {
-            Control h;
-            if ((rc = read_control(c, 0, &h))) return rc;
-        }
         if (flag) return fail(c, MCT_ENUMERIC, "non-finite displacement or velocity after step %lld",
                               (long long)c->steps_enqueued);
         return MCT_OK;
@@ -1844,8 +1845,7 @@ int mct_get_tips(mct_ctx *c, int64_t cap, int32_t *edge, double *xy, int64_t *co
     int32_t nb = 0, total = 0;
     HIP_TRY(c, mct::launch_tips(s.nx, s.ny, s.prm.X, s.prm.Y, s.prm.split, c->dtip_counts, &nb, nullptr, nullptr,
                                 c->dtip_total, 0, c->stream));
-    HIP_TRY(c, hipMemcpyAsync(&total, c->dtip_total, sizeof total, hipMemcpyDeviceToHost, c->stream));
-    HIP_TRY(c, hipStreamSynchronize(c->stream));
+    if (const int rc = fetch_checked(c, &total, c->dtip_total, sizeof total)) return rc;
     *count = total;
     if (cap < total) return fail(c, MCT_ECAPACITY, "%d tips", total);
     if (!total) return MCT_OK;
@@ -1912,24 +1912,20 @@ int mct_get_field(mct_ctx *c, int which, int64_t cap, double *out) {
     if (which < MCT_FIELD_A) {
         // the field of the steps enqueued, with the control block in front: should
         // the device have stopped short of them, its error is returned
-        struct {
-            Control ctl;
-            uint32_t err[4];
-        } v{};
+        ResidentError err{};
         const bool u = which == MCT_FIELD_U, odd = (c->steps_enqueued & 1) != 0;
-        const bool res = c->res.threads != 0;
-        const mct::Fetch::Part parts[3] = {
-            {c->dctl + c->sel, res ? sizeof v : sizeof(Control)},
+        const mct::Fetch::Part parts[4] = {
+            {c->dctl + c->sel, sizeof h},
+            {c->dctl + c->specs.size(), sizeof err},
             {u ? (odd ? s.prm.ux1 : s.prm.ux0) : s.prm.vx, sizeof(double) * s.nn},
             {u ? (odd ? s.prm.uy1 : s.prm.uy0) : s.prm.vy, sizeof(double) * s.nn}};
-        char *const to[3] = {reinterpret_cast<char *>(&v), reinterpret_cast<char *>(out),
-                             reinterpret_cast<char *>(out + s.nn)};
-        HIP_TRY(c, c->fetch.run(c->stream, parts, 3, out, sizeof(double) * 2 * s.nn, [&](int i, size_t off, const char *d, size_t n) {
+        char *const to[4] = {reinterpret_cast<char *>(&h), reinterpret_cast<char *>(&err),
+                             reinterpret_cast<char *>(out), reinterpret_cast<char *>(out + s.nn)};
+        HIP_TRY(c, c->fetch.run(c->stream, parts, 4, out, sizeof(double) * 2 * s.nn, [&](int i, size_t off, const char *d, size_t n) {
             std::memcpy(to[i] + off, d, n);
         }));
-        if (res && v.err[0])
-            return fail(c, MCT_EDEVICE, "resident step: a workgroup did not answer (step %lld)", (long long)v.ctl.base);
-        if (((v.ctl.base ^ c->steps_enqueued) & 1) == 0) return MCT_OK;
+        if (err.word[0]) return resident_failed(c);
+        if (((h.base ^ c->steps_enqueued) & 1) == 0) return MCT_OK;
     }
     if ((rc = read_control(c, c->sel, &h))) return rc;
     if (which >= MCT_FIELD_A) {
@@ -2025,11 +2021,7 @@ int mct_get_split_codes(mct_ctx *c, int64_t cap, uint8_t *out) {
     if (!c->finalized) return fail(c, MCT_ESTATE, "finalize first");
     const Spec &s = cur(c);
     if (cap < s.ne) return fail(c, MCT_ECAPACITY, "need %lld bytes", (long long)s.ne);
-    const mct::Fetch::Part part{s.prm.split, (size_t)s.ne};
-    HIP_TRY(c, c->fetch.run(c->stream, &part, 1, out, (size_t)s.ne, [&](int, size_t off, const char *d, size_t n) {
-        std::memcpy(out + off, d, n);
-    }));
-    return MCT_OK;
+    return fetch_checked(c, out, s.prm.split, (size_t)s.ne);
 }
 
 // checkpoint layout: magic, number of specimens, then per specimen: nodes,
@@ -2058,8 +2050,7 @@ int mct_checkpoint(mct_ctx *c, void *buf, int64_t cap, int64_t *bytes) {
     int rc = widen_state(c);
     if (rc) return rc;
     std::vector<Control> h(S);
-    HIP_TRY(c, hipMemcpyAsync(h.data(), c->dctl, sizeof(Control) * S, hipMemcpyDeviceToHost, c->stream));
-    HIP_TRY(c, hipStreamSynchronize(c->stream));
+    if ((rc = fetch_checked(c, h.data(), c->dctl, sizeof(Control) * S))) return rc;
     int64_t need = 16;
     for (int q = 0; q < S; ++q) {
         const Spec &s = c->specs[q];
@@ -2387,8 +2378,7 @@ int mct_screen_collect(mct_ctx *c, int64_t cap, float *features, int32_t *elem, 
     c->screen_on = on;
     HIP_TRY(c, e);
     int32_t n = 0;
-    HIP_TRY(c, hipMemcpyAsync(&n, c->sd.nrows_last, sizeof n, hipMemcpyDeviceToHost, c->stream));
-    HIP_TRY(c, hipStreamSynchronize(c->stream));
+    if ((rc = fetch_checked(c, &n, c->sd.nrows_last, sizeof n))) return rc;
     *count = n;
     if (n > cap) return fail(c, MCT_ECAPACITY, "%d candidates, capacity %lld", n, (long long)cap);
     if (n == 0) return MCT_OK;

@@ -942,7 +942,9 @@ __global__ __launch_bounds__((resident_threads<T, C>())) void k_resident(const R
         }
     }
 
-    if (stopped) {  // a workgroup did not answer: the state in memory is the launch's first
+    // A workgroup did not answer.  The others may have stored their nodes (in the last
+    // step only one waits for all), so the state in memory is of no use.
+    if (stopped) {
         if (tid == 0) atomicOr(A.err, 1u);
         return;
     }

@@ -947,7 +947,9 @@ __global__ __launch_bounds__(NT) void k_mesh_resident(const MeshArgs A) {
         }
     }
 
-    if (stopped) {  // a workgroup did not answer: the state in memory is the launch's first
+    // A workgroup did not answer.  The others may have stored their nodes (in the last
+    // step only one waits for all), so the state in memory is of no use.
+    if (stopped) {
         if (tid == 0) atomicOr(R.err, 1u);
         return;
     }

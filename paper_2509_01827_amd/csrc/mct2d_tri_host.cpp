@@ -75,20 +75,23 @@ void invalidate(Model &m) {
     m.finalized = false;
 }
 
-int read_ctl(Model &m, Host h, Ctl *out) {
-    // (behind it: the resident step's error word)
-    struct {
-        Ctl c;
-        uint32_t err[2];
-    } d;
-    const Fetch::Part part{m.dctl, sizeof d};
-    TRY(h, m.fetch.run(h.stream, &part, 1, &d, sizeof d, [&](int, size_t off, const char *p, size_t n) {
-        std::memcpy(reinterpret_cast<char *>(&d) + off, p, n);
-    }));
-    if (d.err[0]) return fail(h, MCT_EDEVICE, "resident step: a workgroup did not answer");
-    *out = d.c;
-    return MCT_OK;
+int resident_failed(Host h) {
+    return fail(h, MCT_EDEVICE, "resident step: a workgroup did not answer (the state is undefined until mct_restore)");
 }
+
+// A piece of device memory behind the work enqueued, or the error of a resident
+// launch that gave up (its word lies behind the control block).
+int fetch_checked(Model &m, Host h, void *out, const void *src, size_t bytes) {
+    uint32_t err[2] = {0, 0};
+    const Fetch::Part parts[2] = {{m.dctl + 1, sizeof err}, {src, bytes}};
+    char *const to[2] = {reinterpret_cast<char *>(err), static_cast<char *>(out)};
+    TRY(h, m.fetch.run(h.stream, parts, 2, out, bytes, [&](int i, size_t off, const char *p, size_t n) {
+        std::memcpy(to[i] + off, p, n);
+    }));
+    return err[0] ? resident_failed(h) : MCT_OK;
+}
+
+int read_ctl(Model &m, Host h, Ctl *out) { return fetch_checked(m, h, out, m.dctl, sizeof *out); }
 
 int ensure_eval(Model &m, Host h) {
     if (m.ev.fint) return MCT_OK;
@@ -1086,7 +1089,7 @@ int sync(Model &m, Host h) {
     const double *u = reinterpret_cast<const double *>(m.du[m.steps_enqueued & 1]),
                  *v = reinterpret_cast<const double *>(m.dv);
     TRY(h, launch_check_finite(u, v, u, v, 2 * m.nn, m.dwatch, h.stream));
-    TRY(h, hipMemcpyAsync(&flag, m.dwatch, sizeof flag, hipMemcpyDeviceToHost, h.stream));
+    if ((rc = fetch_checked(m, h, &flag, m.dwatch, sizeof flag))) return rc;
     TRY(h, hipStreamSynchronize(h.stream));
     if (flag)
         return fail(h, MCT_ENUMERIC, "non-finite displacement or velocity after step %lld", (long long)m.steps_enqueued);
@@ -1141,8 +1144,7 @@ int get_tips(Model &m, Host h, int64_t cap, int32_t *edge, double *xy, int64_t *
     if (rc) return rc;
     TRY(h, launch_tip_flags(m.prm, m.dedge_elem, m.ns, m.dtipflag, h.stream));
     std::vector<uint8_t> fl(m.ns);
-    TRY(h, hipMemcpyAsync(fl.data(), m.dtipflag, m.ns, hipMemcpyDeviceToHost, h.stream));
-    TRY(h, hipStreamSynchronize(h.stream));
+    if ((rc = fetch_checked(m, h, fl.data(), m.dtipflag, (size_t)m.ns))) return rc;
     int64_t n = 0;
     for (int64_t s = 0; s < m.ns; ++s) {
         if (!fl[s]) continue;
@@ -1193,7 +1195,7 @@ int get_field(Model &m, Host h, int which, int64_t cap, double *out) {
                     y[q] = xy[2 * q + 1];
                 }
             }));
-            if (d.err[0]) return fail(h, MCT_EDEVICE, "resident step: a workgroup did not answer");
+            if (d.err[0]) return resident_failed(h);
             if (((d.c.base ^ at) & 1) == 0) break;
             at = d.c.base;
         }
@@ -1261,11 +1263,7 @@ int get_energies(Model &m, Host h, double out[4]) {
 int get_split_codes(Model &m, Host h, int64_t cap, uint8_t *out) {
     if (!m.finalized) return fail(h, MCT_ESTATE, "finalize first");
     if (cap < m.ne) return fail(h, MCT_ECAPACITY, "need %lld bytes", (long long)m.ne);
-    const Fetch::Part part{m.dsplit, (size_t)m.ne};
-    TRY(h, m.fetch.run(h.stream, &part, 1, out, (size_t)m.ne, [&](int, size_t off, const char *p, size_t n) {
-        std::memcpy(out + off, p, n);
-    }));
-    return MCT_OK;
+    return fetch_checked(m, h, out, m.dsplit, (size_t)m.ne);
 }
 
 int get_path_geometry(Model &m, Host h, int64_t n, const int32_t *elem, double *out) {

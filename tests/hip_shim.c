@@ -1,0 +1,54 @@
+/* Stands before the HIP runtime in a test's process: counts cooperative
+ * launches, refuses them or an allocation on demand, and remembers the device
+ * memory cleared by the last small hipMemsetAsync of a size. */
+#define _GNU_SOURCE
+#include <dlfcn.h>
+#include <stddef.h>
+
+typedef struct { unsigned x, y, z; } dim3_t;
+
+int shim_refuse_cooperative = 0; /* refuse this many cooperative launches */
+int shim_cooperative = 0;        /* cooperative launches let through */
+size_t shim_refuse_bytes = 0;    /* refuse allocations of this size */
+size_t shim_watch_bytes = 0;     /* hipMemsetAsync of this size: */
+void *shim_cleared = NULL;       /* the memory it last cleared */
+
+static void *next_of(const char *name) {
+    void *f = dlsym(RTLD_NEXT, name);
+    if (!f) {
+        void *h = dlopen("libamdhip64.so.7", RTLD_NOLOAD | RTLD_LAZY);
+        if (!h) h = dlopen("libamdhip64.so", RTLD_NOLOAD | RTLD_LAZY);
+        if (h) f = dlsym(h, name);
+    }
+    return f;
+}
+
+int hipLaunchCooperativeKernel(const void *f, dim3_t grid, dim3_t block, void **args, unsigned lds, void *stream) {
+    static int (*real)(const void *, dim3_t, dim3_t, void **, unsigned, void *) = NULL;
+    if (!real) real = (int (*)(const void *, dim3_t, dim3_t, void **, unsigned, void *))next_of("hipLaunchCooperativeKernel");
+    if (shim_refuse_cooperative > 0) {
+        --shim_refuse_cooperative;
+        return 720; /* hipErrorCooperativeLaunchTooLarge */
+    }
+    ++shim_cooperative;
+    return real(f, grid, block, args, lds, stream);
+}
+
+int hipMalloc(void **p, size_t bytes) {
+    static int (*real)(void **, size_t) = NULL;
+    if (!real) real = (int (*)(void **, size_t))next_of("hipMalloc");
+    if (shim_refuse_bytes && bytes == shim_refuse_bytes) return 2; /* hipErrorOutOfMemory */
+    return real(p, bytes);
+}
+
+int hipMemsetAsync(void *p, int value, size_t bytes, void *stream) {
+    static int (*real)(void *, int, size_t, void *) = NULL;
+    if (!real) real = (int (*)(void *, int, size_t, void *))next_of("hipMemsetAsync");
+    if (bytes == shim_watch_bytes) shim_cleared = p;
+    return real(p, value, bytes, stream);
+}
+
+int shim_poke(void *p, unsigned value) { /* writes a 32-bit word of device memory */
+    int (*copy)(void *, const void *, size_t, int) = (int (*)(void *, const void *, size_t, int))next_of("hipMemcpy");
+    return p ? copy(p, &value, sizeof value, 1 /* host to device */) : 1;
+}
