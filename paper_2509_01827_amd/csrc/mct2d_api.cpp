@@ -1656,7 +1656,6 @@ int mct_step(mct_ctx *c, int64_t n) {
             const int m = (int)std::min<int64_t>(left, mct::kResidentMaxSteps);
             HIP_TRY(c, mct::launch_resident(c->res, launch_of(c), m, (int)(c->steps_enqueued & 1), c->res_epoch,
                                             c->stream));
-            c->res_epoch += (uint32_t)m;
             c->steps_enqueued += m;
             left -= m;
         }

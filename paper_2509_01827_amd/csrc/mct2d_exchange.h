@@ -10,6 +10,12 @@
 // is overwritten by epoch e + 2, which its writer reaches only after every
 // reader has published epoch e + 1, that is, has read epoch e.
 //
+// A tag stands for one epoch only: the buffers start as zeros, epoch 0 is never
+// sent, and before the tags run out the host clears the buffers between two
+// launches and counts from 0 again (next_epochs).  Otherwise a word that was
+// not written since (a slot without a candidate is one word of four) could
+// carry the wanted tag.
+//
 // One store-to-load hand-over was measured at 1.0 us over 8 workgroups and
 // 1.3 to 1.7 us over 256 (200 nodes and one candidate slot each, words of one
 // kind contiguous; 3.4 us with a node's words side by side, whose 8-byte
@@ -44,6 +50,17 @@ __device__ __forceinline__ void put(uint64_t *p, uint64_t w) {
 }
 __device__ __forceinline__ uint64_t get(const uint64_t *p) {
     return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+
+// Before a launch that sends the epochs epoch + 1 .. epoch + n (n far below the
+// number of tags) through these buffers.
+inline hipError_t next_epochs(uint32_t &epoch, int n, uint64_t *xb, size_t words_u, uint64_t *slots, size_t words_s,
+                              hipStream_t st) {
+    if (epoch + (uint32_t)n <= kTagMask) return hipSuccess;
+    hipError_t e = hipMemsetAsync(xb, 0, sizeof(uint64_t) * words_u, st);
+    if (e == hipSuccess) e = hipMemsetAsync(slots, 0, sizeof(uint64_t) * words_s, st);
+    if (e == hipSuccess) epoch = 0;
+    return e;
 }
 
 // A pair of values (a node's two components) as words `stride` apart:

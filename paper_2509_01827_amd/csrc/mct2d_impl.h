@@ -198,8 +198,9 @@ hipError_t launch_commit(const Launch &L, int n, hipStream_t s);
 // The resident step (mct2d_resident.hip): n steps of a plain grid in one
 // cooperative launch, a tile of nodes per workgroup for all of them.  A plan
 // holds the tiles and the exchange buffers (words_u and words_s words, zeroed
-// when allocated; err: set when a workgroup did not answer).  epoch0 grows by
-// the steps of each launch on the same buffers, starting at 0.
+// when allocated; err: set when a workgroup did not answer).  epoch: the steps
+// launched on the buffers since they were cleared, advanced by each launch (which
+// clears them again now and then).
 constexpr int kResidentMaxTiles = 256;
 constexpr int kResidentMaxSteps = 512;  // per launch
 struct ResidentPlan {
@@ -213,7 +214,7 @@ struct ResidentPlan {
 // false: the grid is too large for the chip (or the device has no
 // cooperative launch).
 bool resident_plan(int nx, int ny, bool f32, bool subcell, int device, ResidentPlan &r);
-hipError_t launch_resident(const ResidentPlan &r, const Launch &L, int n, int par0, uint32_t epoch0, hipStream_t s);
+hipError_t launch_resident(const ResidentPlan &r, const Launch &L, int n, int par0, uint32_t &epoch, hipStream_t s);
 
 // Uniform-lattice check of one specimen: ref receives element 0's geometry
 // (LatticeConst), flag bit 0 = some element differs bitwise, bit 1 = the

@@ -996,20 +996,24 @@ const void *resident_kernel(const ResidentPlan &r) {
 }
 
 template <class T>
-hipError_t launch(const ResidentPlan &r, const StepParamsT<T> &p, int n, int par0, uint32_t epoch0, hipStream_t st) {
+hipError_t launch(const ResidentPlan &r, const StepParamsT<T> &p, int n, int par0, uint32_t &epoch, hipStream_t st) {
+    hipError_t e = xch::next_epochs(epoch, n, r.xb, r.words_u, r.slots, r.words_s, st);
+    if (e != hipSuccess) return e;
     ResidentArgs<T> a;
     a.p = p;
     a.ntx = r.ntx;
     a.nwg = r.ntx * r.nty;
     a.n = n;
     a.par0 = par0;
-    a.epoch0 = epoch0;
+    a.epoch0 = epoch;
     a.xb = r.xb;
     a.slots = r.slots;
     a.err = r.err;
     void *args[] = {&a};
     (void)hipGetLastError();
-    return hipLaunchCooperativeKernel(resident_kernel(r), dim3(a.nwg), dim3(r.threads), args, (unsigned)r.lds, st);
+    e = hipLaunchCooperativeKernel(resident_kernel(r), dim3(a.nwg), dim3(r.threads), args, (unsigned)r.lds, st);
+    if (e == hipSuccess) epoch += (uint32_t)n;
+    return e;
 }
 
 }  // namespace
@@ -1056,8 +1060,8 @@ bool resident_plan(int nx, int ny, bool f32, bool subcell, int device, ResidentP
     return (int64_t)per_cu * cus >= (int64_t)r.ntx * r.nty;
 }
 
-hipError_t launch_resident(const ResidentPlan &r, const Launch &L, int n, int par0, uint32_t epoch0, hipStream_t st) {
-    return L.f32 ? launch<float>(r, L.p0f, n, par0, epoch0, st) : launch<double>(r, L.p0, n, par0, epoch0, st);
+hipError_t launch_resident(const ResidentPlan &r, const Launch &L, int n, int par0, uint32_t &epoch, hipStream_t st) {
+    return L.f32 ? launch<float>(r, L.p0f, n, par0, epoch, st) : launch<double>(r, L.p0, n, par0, epoch, st);
 }
 
 }  // namespace mct

@@ -1046,18 +1046,24 @@ bool mesh_resident_fits(ResidentMesh &r, int nv, int device) {
     return (int64_t)per_cu * cus >= r.npatch;
 }
 
-hipError_t launch_mesh_resident(const Params &p, const ResidentMesh &r, int n, int par0, uint32_t epoch0,
+hipError_t launch_mesh_resident(const Params &p, const ResidentMesh &r, int n, int par0, uint32_t &epoch,
                                 hipStream_t st) {
+    const size_t words = 2 * (size_t)r.npatch;  // of one kind, both parities
+    hipError_t e = xch::next_epochs(epoch, n, r.xb, words * xch::pair_words<double>() * r.cap, r.slots,
+                                    words * xch::kSlotWords, st);
+    if (e != hipSuccess) return e;
     MeshArgs a;
     a.p = p;
     a.r = r;
     a.n = n;
     a.par0 = par0;
-    a.epoch0 = epoch0;
+    a.epoch0 = epoch;
     void *args[] = {&a};
     (void)hipGetLastError();
-    return hipLaunchCooperativeKernel(mesh_kernel(p.nv, r.threads, r.wmax), dim3(r.npatch), dim3(r.threads), args,
-                                      (unsigned)r.lds, st);
+    e = hipLaunchCooperativeKernel(mesh_kernel(p.nv, r.threads, r.wmax), dim3(r.npatch), dim3(r.threads), args,
+                                   (unsigned)r.lds, st);
+    if (e == hipSuccess) epoch += (uint32_t)n;
+    return e;
 }
 
 }  // namespace tri

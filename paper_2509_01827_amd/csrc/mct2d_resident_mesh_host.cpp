@@ -237,6 +237,7 @@ bool build(const Model &m, int parts, int threads, int slots, int device, Reside
 void free_resident(Model &m) {
     if (m.res.tables) (void)hipFree(m.res.tables);
     m.res = ResidentMesh{};
+    m.res_epoch = 0;  // (new buffers are cleared)
 }
 
 // Builds the resident step's patches where it applies (automatic kernels, the

@@ -185,9 +185,10 @@ struct ResidentMesh {
 };
 // LDS layout and launch limits; np_max may be raised.
 bool mesh_resident_fits(ResidentMesh &r, int nv, int device);
-// n <= kMeshResidentSteps steps from ctl->base, u^base in buffer par0; takes
-// the epochs epoch0 .. epoch0 + n.
-hipError_t launch_mesh_resident(const Params &p, const ResidentMesh &r, int n, int par0, uint32_t epoch0,
+// n <= kMeshResidentSteps steps from ctl->base, u^base in buffer par0; epoch: the
+// steps launched on the exchange buffers since they were cleared, advanced by n
+// (now and then they are cleared again).
+hipError_t launch_mesh_resident(const Params &p, const ResidentMesh &r, int n, int par0, uint32_t &epoch,
                                 hipStream_t st);
 
 // One time step j of the running segment (step index ctl->base + j):

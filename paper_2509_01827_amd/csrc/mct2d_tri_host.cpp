@@ -1028,7 +1028,6 @@ int step(Model &m, Host h, int64_t n) {
         while (left > 0) {
             const int k = (int)std::min<int64_t>(left, kMeshResidentSteps);
             TRY(h, launch_mesh_resident(m.prm, m.res, k, (int)(m.steps_enqueued & 1), m.res_epoch, h.stream));
-            m.res_epoch += (uint32_t)k;
             m.steps_enqueued += k;
             left -= k;
         }

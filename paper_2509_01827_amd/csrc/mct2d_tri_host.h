@@ -87,7 +87,7 @@ struct Model {
     hipGraphExec_t graph = nullptr;
     int64_t steps_enqueued = 0;
     ResidentMesh res;        // the resident step's patches (automatic kernels, where they fit)
-    uint32_t res_epoch = 0;  // of the state in memory (exchange tags)
+    uint32_t res_epoch = 0;  // steps launched on its exchange buffers since they were cleared
     Fetch fetch;             // query results to the host
 };
 
