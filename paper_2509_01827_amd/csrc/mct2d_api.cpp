@@ -467,8 +467,12 @@ int plan_resident(mct_ctx *c) {
     if (c->batch || c->tile_req != 0 || p.sct || p.front || p.near) return MCT_OK;
     mct::ResidentPlan r;
     if (!mct::resident_plan(p.nx, p.ny, c->precision == 32, p.subcell != 0, c->device, r)) return MCT_OK;
-    HIP_TRY(c, hipMalloc((void **)&c->res.xb, sizeof(uint64_t) * r.words_u));
-    HIP_TRY(c, hipMalloc((void **)&c->res.slots, sizeof(uint64_t) * r.words_s));
+    if (hipMalloc((void **)&c->res.xb, sizeof(uint64_t) * r.words_u) != hipSuccess ||
+        hipMalloc((void **)&c->res.slots, sizeof(uint64_t) * r.words_s) != hipSuccess) {
+        (void)hipGetLastError();
+        free_resident(c);
+        return MCT_OK;  // the per-step kernels need none of it
+    }
     r.xb = c->res.xb;
     r.slots = c->res.slots;
     r.err = reinterpret_cast<uint32_t *>(c->dctl + 1);
@@ -1654,12 +1658,16 @@ int mct_step(mct_ctx *c, int64_t n) {
         hipStreamIsCapturing(c->stream, &cap) == hipSuccess && cap == hipStreamCaptureStatusNone) {
         while (left > 0) {
             const int m = (int)std::min<int64_t>(left, mct::kResidentMaxSteps);
-            HIP_TRY(c, mct::launch_resident(c->res, launch_of(c), m, (int)(c->steps_enqueued & 1), c->res_epoch,
-                                            c->stream));
+            if (mct::launch_resident(c->res, launch_of(c), m, (int)(c->steps_enqueued & 1), c->res_epoch, c->stream) !=
+                hipSuccess) {  // refused: the per-step kernels take over until the next plan
+                (void)hipGetLastError();
+                c->res.threads = 0;
+                break;
+            }
             c->steps_enqueued += m;
             left -= m;
         }
-        return MCT_OK;
+        if (left == 0) return MCT_OK;
     }
     if (c->use_graph) {
         while (left >= kGraphSteps) {

@@ -1027,11 +1027,16 @@ int step(Model &m, Host h, int64_t n) {
         hipStreamIsCapturing(h.stream, &cap) == hipSuccess && cap == hipStreamCaptureStatusNone) {
         while (left > 0) {
             const int k = (int)std::min<int64_t>(left, kMeshResidentSteps);
-            TRY(h, launch_mesh_resident(m.prm, m.res, k, (int)(m.steps_enqueued & 1), m.res_epoch, h.stream));
+            if (launch_mesh_resident(m.prm, m.res, k, (int)(m.steps_enqueued & 1), m.res_epoch, h.stream) !=
+                hipSuccess) {  // refused: the per-step kernels take over until the next plan
+                (void)hipGetLastError();
+                m.res.threads = 0;
+                break;
+            }
             m.steps_enqueued += k;
             left -= k;
         }
-        return MCT_OK;
+        if (left == 0) return MCT_OK;
     }
     if (m.use_graph) {
         while (left >= kGraphSteps) {

@@ -1,15 +1,16 @@
 /* Stands before the HIP runtime in a test's process: counts cooperative
- * launches, refuses them or an allocation on demand, and remembers the device
- * memory cleared by the last small hipMemsetAsync of a size. */
+ * launches and allocations, refuses them on demand, and remembers the device
+ * memory cleared by the last hipMemsetAsync of a size. */
 #define _GNU_SOURCE
 #include <dlfcn.h>
 #include <stddef.h>
 
 typedef struct { unsigned x, y, z; } dim3_t;
 
-int shim_refuse_cooperative = 0; /* refuse this many cooperative launches */
-int shim_cooperative = 0;        /* cooperative launches let through */
-size_t shim_refuse_bytes = 0;    /* refuse allocations of this size */
+int shim_cooperative = 0;        /* cooperative launches asked for */
+int shim_refuse_launch = 0;      /* refuse the one that would be this many (0: none) */
+int shim_mallocs = 0;            /* allocations asked for */
+int shim_refuse_malloc = 0;      /* refuse the one that would be this many (0: none) */
 size_t shim_watch_bytes = 0;     /* hipMemsetAsync of this size: */
 void *shim_cleared = NULL;       /* the memory it last cleared */
 
@@ -26,18 +27,14 @@ static void *next_of(const char *name) {
 int hipLaunchCooperativeKernel(const void *f, dim3_t grid, dim3_t block, void **args, unsigned lds, void *stream) {
     static int (*real)(const void *, dim3_t, dim3_t, void **, unsigned, void *) = NULL;
     if (!real) real = (int (*)(const void *, dim3_t, dim3_t, void **, unsigned, void *))next_of("hipLaunchCooperativeKernel");
-    if (shim_refuse_cooperative > 0) {
-        --shim_refuse_cooperative;
-        return 720; /* hipErrorCooperativeLaunchTooLarge */
-    }
-    ++shim_cooperative;
+    if (++shim_cooperative == shim_refuse_launch) return 720; /* hipErrorCooperativeLaunchTooLarge */
     return real(f, grid, block, args, lds, stream);
 }
 
 int hipMalloc(void **p, size_t bytes) {
     static int (*real)(void **, size_t) = NULL;
     if (!real) real = (int (*)(void **, size_t))next_of("hipMalloc");
-    if (shim_refuse_bytes && bytes == shim_refuse_bytes) return 2; /* hipErrorOutOfMemory */
+    if (++shim_mallocs == shim_refuse_malloc) return 2; /* hipErrorOutOfMemory */
     return real(p, bytes);
 }
 
