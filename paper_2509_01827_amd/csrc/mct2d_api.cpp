@@ -460,11 +460,13 @@ int set_launch_geometry(mct_ctx *c) {
 // The resident step runs the automatic launch choice of a plain grid that
 // fits on the chip, with the global pick; a chosen tile shape, single-tip
 // tracking, the per-front pick and the near-threshold log keep the per-step
-// kernels (as do requests without graphs, which a caller may capture).
+// kernels (as do requests without graphs, which a caller may capture, and
+// streams with a mask of compute units).
 int plan_resident(mct_ctx *c) {
     free_resident(c);
     const StepParams &p = c->specs[0].prm;
-    if (c->batch || c->tile_req != 0 || p.sct || p.front || p.near) return MCT_OK;
+    if (c->batch || c->tile_req != 0 || p.sct || p.front || p.near || !mct::whole_device(c->stream, c->device))
+        return MCT_OK;
     mct::ResidentPlan r;
     if (!mct::resident_plan(p.nx, p.ny, c->precision == 32, p.subcell != 0, c->device, r)) return MCT_OK;
     if (hipMalloc((void **)&c->res.xb, sizeof(uint64_t) * r.words_u) != hipSuccess ||

@@ -211,6 +211,11 @@ struct ResidentPlan {
     uint64_t *xb = nullptr, *slots = nullptr;
     uint32_t *err = nullptr;
 };
+// Whether work in the stream may use every compute unit of the device.  A
+// resident launch is planned for the whole device and needs all its workgroups
+// on the chip at once, so a stream with a mask of compute units keeps the
+// per-step kernels.
+bool whole_device(hipStream_t s, int device);
 // false: the grid is too large for the chip (or the device has no
 // cooperative launch).
 bool resident_plan(int nx, int ny, bool f32, bool subcell, int device, ResidentPlan &r);

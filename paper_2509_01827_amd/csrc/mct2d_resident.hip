@@ -38,6 +38,7 @@
 
 #include <algorithm>
 #include <climits>
+#include <vector>
 
 namespace mct {
 
@@ -1030,6 +1031,20 @@ bool tiles_fit(int nx, int ny, int most, ResidentPlan &r) {
     r.words_u = 2 * ntx * nty * R::cap * (r.f32 ? xch::pair_words<float>() : xch::pair_words<double>());
     r.words_s = 2 * ntx * nty * xch::kSlotWords;
     r.lds = r.f32 ? Res<float, C>::total : Res<double, C>::total;
+    return true;
+}
+
+bool whole_device(hipStream_t s, int device) {
+    if (s == hipStreamLegacy || s == hipStreamPerThread) return true;  // (the query takes streams of their own only)
+    int cus = 0;
+    if (hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, device) != hipSuccess) return false;
+    std::vector<uint32_t> mask((size_t)(cus + 31) / 32, 0u);
+    if (hipExtStreamGetCUMask(s, (uint32_t)mask.size(), mask.data()) != hipSuccess) {
+        (void)hipGetLastError();
+        return false;
+    }
+    for (int i = 0; i < cus; ++i)
+        if (!((mask[i / 32] >> (i % 32)) & 1u)) return false;
     return true;
 }
 

@@ -11,6 +11,7 @@
 #include <numeric>
 #include <type_traits>
 
+#include "mct2d_impl.h"
 #include "mct2d_tri_host.h"
 
 namespace mct {
@@ -248,6 +249,7 @@ hipError_t plan_resident(Model &m, hipStream_t stream) {
     int dev = 0;
     hipError_t e = hipGetDevice(&dev);
     if (e != hipSuccess) return e;
+    if (!whole_device(stream, dev)) return hipSuccess;
     ResidentMesh r;
     Tables t;
     bool ok = false;

@@ -49,3 +49,10 @@ int shim_poke(void *p, unsigned value) { /* writes a 32-bit word of device memor
     int (*copy)(void *, const void *, size_t, int) = (int (*)(void *, const void *, size_t, int))next_of("hipMemcpy");
     return p ? copy(p, &value, sizeof value, 1 /* host to device */) : 1;
 }
+
+void *shim_masked_stream(unsigned words, const unsigned *mask) { /* a stream on some compute units */
+    int (*create)(void **, unsigned, const unsigned *) =
+        (int (*)(void **, unsigned, const unsigned *))next_of("hipExtStreamCreateWithCUMask");
+    void *s = NULL;
+    return create(&s, words, mask) == 0 ? s : NULL;
+}
