@@ -8,6 +8,7 @@
 // kernel's threads, tables or LDS keeps the per-step kernels.
 #include <algorithm>
 #include <cstring>
+#include <new>
 #include <numeric>
 #include <type_traits>
 
@@ -67,6 +68,7 @@ uint2 pack16(const int v[4]) {
 bool build(const Model &m, int parts, int threads, int slots, int device, ResidentMesh &r, Tables &t) {
     const int nv = m.nv;
     const int64_t nn = m.nn, ne = m.ne;
+    if (nn > (int64_t)parts * threads || ne > (int64_t)parts * slots) return false;  // (before any work on a large mesh)
     r = ResidentMesh{};
     r.threads = threads;
     r.npatch = parts;
@@ -233,6 +235,8 @@ bool build(const Model &m, int parts, int threads, int slots, int device, Reside
     return true;
 }
 
+hipError_t plan(Model &m, hipStream_t stream);
+
 }  // namespace
 
 void free_resident(Model &m) {
@@ -245,6 +249,16 @@ void free_resident(Model &m) {
 // global pick of every tip); leaves m.res.threads 0 otherwise.
 hipError_t plan_resident(Model &m, hipStream_t stream) {
     free_resident(m);
+    try {
+        return plan(m, stream);
+    } catch (const std::bad_alloc &) {  // no memory for the tables: the per-step kernels need none of them
+        return hipSuccess;
+    }
+}
+
+namespace {
+
+hipError_t plan(Model &m, hipStream_t stream) {
     if (m.kernels != 0 || m.sct || m.front_rho > 0 || m.ne == 0) return hipSuccess;
     int dev = 0;
     hipError_t e = hipGetDevice(&dev);
@@ -328,5 +342,6 @@ hipError_t plan_resident(Model &m, hipStream_t stream) {
     return hipSuccess;
 }
 
+}  // namespace
 }  // namespace tri
 }  // namespace mct
