@@ -402,10 +402,11 @@ int mct_restore(mct_ctx *ctx, const void *host_buf, int64_t bytes);
  * units' shares); 0 = automatic (5).  The environment
  * variable MCT_PATCH_NODES, read when the choice is made, sets the patch
  * size of choice 5 instead (1..256 nodes; a testing and tuning knob).
- * With the automatic choice and graphs, a plain grid of up to about 240 000
- * nodes with the global pick takes requests of several steps in one
- * cooperative launch that keeps the state on the chip (mct_get_launch reports
- * the tile of the per-step kernels, which run the other requests).
+ * With the automatic choice and graphs, a plain grid of up to about 180 000
+ * nodes (binary32: 245 000) or a mesh that fits the chip, with the global
+ * pick, takes requests of several steps in one cooperative launch that keeps
+ * the state on the chip (mct_get_launch reports the tile of the per-step
+ * kernels, which run the other requests).
  * Results do not depend on any of these choices (fixed summation orders).
  * Errors: MCT_EINVAL for a tile index out of range (0..5 on an
  * unstructured mesh). */

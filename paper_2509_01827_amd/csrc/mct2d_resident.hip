@@ -97,16 +97,13 @@ struct Res {
     static constexpr int NR = TXE * TYE, NH = TXE * (TYE + 1), NS = NH + (TXE + 1) * TYE;
     static constexpr int NO = 2 * (TXE + TYE), HN = HX * HY;
     static constexpr int cap = 4 * (TX + TY);  // nodes sent: stride of the words of one kind
-    // the large binary64 tiles keep fewer candidates' normals, the largest also
-    // the forces over the stresses (one more barrier): their LDS would not fit
-    // into 160 KB otherwise
-    static constexpr bool ALIAS = sizeof(T) == 8 && C > 768;
+    // the large binary64 tiles keep fewer candidates' normals: their LDS would not
+    // fit into 160 KB otherwise
     static constexpr int NC = sizeof(T) == 8 && C > 512 ? 96 : C < 512 ? 384 : 256;  // candidates that keep their normals
     static constexpr int up(int n) { return (n + 15) & ~15; }
     static constexpr int S = (int)sizeof(T);
     static constexpr int u = 0, xy = u + up(2 * HN * S), e = xy + up(2 * HN * S);
-    static constexpr int fe = ALIAS ? e : e + up(3 * NS * S);
-    static constexpr int og = fe + up((8 * NR > 3 * NS ? 8 * NR : 3 * NS) * S), cn = og + up(13 * NO * S);
+    static constexpr int fe = e + up(3 * NS * S), og = fe + up(8 * NR * S), cn = og + up(13 * NO * S);
     static constexpr int ci = cn + up(8 * NC * S), gc = ci + up(32 * NC), bc = gc + up(NR * S), cand = bc + up(4 * cap * S);
     static constexpr int splitl = cand + up(4 * TX * TY * 2), split = splitl + up(NR * 2);
     static constexpr int code = split + up(EX * EY), total = code + up(NT);
@@ -497,7 +494,7 @@ __global__ __launch_bounds__((resident_threads<T, C>())) void k_resident(const R
     if (ie >= 1 && je >= 1 && code == 0)
         for (int k = 0; k < 4; ++k)
             if ((nbs >> k) & 1u) s_cand[atomicAdd(&s_ncand, 1)] = (uint16_t)((tid << 2) | k);
-    if (code == kAbsent && ring && !R::ALIAS)
+    if (code == kAbsent && ring)
         for (int c = 0; c < 8; ++c) s_fe[c * NR + tid] = T(0);
 
     // every load of the set-up done: a wait for one of them in the loop would
@@ -797,13 +794,9 @@ __global__ __launch_bounds__((resident_threads<T, C>())) void k_resident(const R
                 }
             }
         }
-        if constexpr (R::ALIAS) __syncthreads();  // the stresses are no longer read
         if (code == 0) {
 #pragma unroll
             for (int c = 0; c < 8; ++c) s_fe[c * NR + tid] = fe[c];
-        } else if (R::ALIAS && code == kAbsent && ring) {
-#pragma unroll
-            for (int c = 0; c < 8; ++c) s_fe[c * NR + tid] = T(0);
         }
         // split elements: a constant-strain triangle per corner split, then a
         // bar per piece of a through split
@@ -987,8 +980,9 @@ const void *resident_kernel(int c) {
         case 256: return reinterpret_cast<const void *>(k_resident<T, 256, SC>);
         case 512: return reinterpret_cast<const void *>(k_resident<T, 512, SC>);
         case 768: return reinterpret_cast<const void *>(k_resident<T, 768, SC>);
-        default: return reinterpret_cast<const void *>(k_resident<T, 1024, SC>);
     }
+    if constexpr (sizeof(T) == 4) return reinterpret_cast<const void *>(k_resident<T, 1024, SC>);
+    return nullptr;
 }
 
 const void *resident_kernel(const ResidentPlan &r) {
@@ -1019,19 +1013,35 @@ hipError_t launch(const ResidentPlan &r, const StepParamsT<T> &p, int n, int par
 
 }  // namespace
 
-template <int C>
+template <class T, int C>
 bool tiles_fit(int nx, int ny, int most, ResidentPlan &r) {
-    using R = Res<float, C>;  // the same shapes in both precisions
+    using R = Res<T, C>;
     const int64_t ntx = (nx + R::TXE - 1) / R::TX, nty = (ny + R::TYE - 1) / R::TY;
     if (ntx * nty > most) return false;
     r.tile = C;
-    r.threads = r.f32 ? Res<float, C>::NT : Res<double, C>::NT;
+    r.threads = R::NT;
     r.ntx = (int)ntx;
     r.nty = (int)nty;
-    r.words_u = 2 * ntx * nty * R::cap * (r.f32 ? xch::pair_words<float>() : xch::pair_words<double>());
+    r.words_u = 2 * ntx * nty * R::cap * xch::pair_words<T>();
     r.words_s = 2 * ntx * nty * xch::kSlotWords;
-    r.lds = r.f32 ? Res<float, C>::total : Res<double, C>::total;
+    r.lds = R::total;
     return true;
+}
+
+// The smallest tiles of which there is at most one per compute unit: fewer
+// wavefronts are fewer instructions per SIMD and step.  us per step, square grids
+// at both ends of a class (per-step kernels in brackets): binary64 class 256 at
+// 239 x 239 elements 4.0 (9.5), 512 at 240 and 335 5.0 (10.6) and 5.2 (12.0), 768
+// at 336 and 415 6.4 (12.1) and 6.6 (13.0).  Tiles of 1 024 elements, four
+// wavefronts per SIMD and 128 registers, spill 93 of them in binary64: 17.8 (13.1)
+// at 416, 19.6 (16.7) at 495, so there they are for binary32 only, 4.7 (10.6)
+// and 4.7 (11.8).
+template <class T>
+bool tiles_fit(int nx, int ny, int most, ResidentPlan &r) {
+    if (tiles_fit<T, 256>(nx, ny, most, r) || tiles_fit<T, 512>(nx, ny, most, r) || tiles_fit<T, 768>(nx, ny, most, r))
+        return true;
+    if constexpr (sizeof(T) == 4) return tiles_fit<T, 1024>(nx, ny, most, r);
+    return false;
 }
 
 bool whole_device(hipStream_t s, int device) {
@@ -1048,8 +1058,6 @@ bool whole_device(hipStream_t s, int device) {
     return true;
 }
 
-// The plan for a grid: the smallest tiles of which there is at most one per
-// compute unit (fewer wavefronts are fewer instructions per SIMD and step).
 bool resident_plan(int nx, int ny, bool f32, bool subcell, int device, ResidentPlan &r) {
     r = ResidentPlan{};
     r.f32 = f32;
@@ -1058,9 +1066,7 @@ bool resident_plan(int nx, int ny, bool f32, bool subcell, int device, ResidentP
     if (hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, device) != hipSuccess) return false;
     if (hipDeviceGetAttribute(&coop, hipDeviceAttributeCooperativeLaunch, device) != hipSuccess || !coop) return false;
     const int most = std::min(cus, kResidentMaxTiles);
-    if (!tiles_fit<256>(nx, ny, most, r) && !tiles_fit<512>(nx, ny, most, r) && !tiles_fit<768>(nx, ny, most, r) &&
-        !tiles_fit<1024>(nx, ny, most, r))
-        return false;
+    if (!(f32 ? tiles_fit<float>(nx, ny, most, r) : tiles_fit<double>(nx, ny, most, r))) return false;
     const void *k = resident_kernel(r);
     if (r.lds > 65536 &&
         hipFuncSetAttribute(k, hipFuncAttributeMaxDynamicSharedMemorySize, r.lds) != hipSuccess) {
