@@ -30,7 +30,15 @@ using mct::StepParams;
 namespace {
 
 constexpr int kGraphSteps = 64;  // steps per captured graph segment
-constexpr int64_t kResidentMinSteps = 4;  // shorter requests take the per-step kernels
+
+// Fewest steps of a request that the resident step takes; shorter ones take the
+// per-step kernels.  A resident launch costs some 24 us beside its steps and saves
+// 5 us a step on grids of a few tiles, where the per-step launches themselves
+// bound the step, and 6 to 9 on larger ones.  us per request, one after another,
+// resident and per step: 40 x 40 elements (9 tiles) 36.5 and 35.0 for 5 steps,
+// 39.4 and 40.1 for 6; 16 x 16 (4 tiles) 35.8 and 33.9, 38.6 and 38.8; 80 x 80 (36
+// tiles) 37.1 and 44.1 for 4; 400 x 400 46.6 and 45.3 for 3, 52.7 and 56.8 for 4.
+int64_t resident_min_steps(const mct::ResidentPlan &r) { return r.ntx * r.nty < 32 ? 6 : 4; }
 constexpr int kNumOrders = 3;    // work-unit orders of a batch (see build_units)
 
 struct TractionEdge {
@@ -1656,7 +1664,7 @@ int mct_step(mct_ctx *c, int64_t n) {
     if (c->screen_on) return step_screened(c, n);
     int64_t left = n;
     hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
-    if (c->use_graph && c->res.threads && n >= kResidentMinSteps &&
+    if (c->use_graph && c->res.threads && n >= resident_min_steps(c->res) &&
         hipStreamIsCapturing(c->stream, &cap) == hipSuccess && cap == hipStreamCaptureStatusNone) {
         while (left > 0) {
             const int m = (int)std::min<int64_t>(left, mct::kResidentMaxSteps);
@@ -2320,7 +2328,7 @@ int mct_autotune(mct_ctx *c, int trial_steps, int *tile_out, int *order_out, dou
             if (t == 0 && !c->res.threads) continue;
             const int trial = t == 0 ? std::max(trial_steps, 64) : trial_steps;
             if ((rc = mct_restore(c, ck.data(), bytes))) break;
-            if ((rc = mct_step(c, t == 0 ? kResidentMinSteps : 2))) break;  // warm
+            if ((rc = mct_step(c, t == 0 ? resident_min_steps(c->res) : 2))) break;  // warm
             if (hipEventRecord(e0, c->stream) != hipSuccess) rc = MCT_EDEVICE;
             if (!rc) rc = mct_step(c, trial);
             if (!rc && hipEventRecord(e1, c->stream) != hipSuccess) rc = MCT_EDEVICE;

@@ -23,6 +23,25 @@ for nx, ny, kw, resident in ((415, 431, {}, True), (416, 431, {}, False), (495, 
     m.close()
 """
 
+STEPS = """
+# fewest steps: 6 on fewer than 32 tiles (15 x 15 nodes each), 4 on more; 10 on meshes
+tri = W.tri_plate(40, 16, 0.1, 0.04, notch_len=0.05, traction=8.0e6)
+for cfg, least in (((20, 16), 6), ((74, 89), 6), ((75, 89), 4), ((300, 187), 4), (tri, 10)):
+    if isinstance(cfg, tuple):
+        cfg = W.plate(*cfg, 1.0e-4 * cfg[0], 1.0e-4 * cfg[1], traction=2.0e7, notch_len=cfg[0] // 2, name="route")
+    m, ref = mct2d.from_config(cfg), mct2d.from_config(cfg, tile=1)
+    word("shim_cooperative", 0)
+    m.step(least - 1)
+    m.sync()
+    assert word("shim_cooperative") == 0, least
+    m.step(least)
+    m.sync()
+    assert word("shim_cooperative") == 1, least
+    ref.step(2 * least - 1)
+    assert all(np.array_equal(a, b) for a, b in zip(state(m), state(ref)))
+"""
 
-def test_grid_sizes(tmp_path):
-    run(SIZES, tmp_path)
+
+@pytest.mark.parametrize("code", [SIZES, STEPS], ids=["sizes", "steps"])
+def test_routes(code, tmp_path):
+    run(code, tmp_path)
