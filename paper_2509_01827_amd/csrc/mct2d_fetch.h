@@ -14,6 +14,7 @@
 #include <cstring>
 #include <memory>
 #include <new>
+#include <utility>
 
 namespace mct {
 
@@ -35,7 +36,16 @@ class Fetch {
         size_t bytes;
     };
 
+    Fetch() = default;
     ~Fetch() { release(); }
+    // (moved with its model: the buffers have one owner)
+    Fetch(Fetch &&o) noexcept { *this = std::move(o); }
+    Fetch &operator=(Fetch &&o) noexcept {
+        std::swap(buf_, o.buf_);
+        std::swap(half_, o.half_);
+        std::swap(ev_, o.ev_);
+        return *this;
+    }
 
     // Buffers for results of up to `bytes` (kept; at most two of kHalf).  Without
     // them (no pinned memory to be had) run() copies into pageable memory.

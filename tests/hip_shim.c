@@ -11,6 +11,7 @@ int shim_cooperative = 0;        /* cooperative launches asked for */
 int shim_refuse_launch = 0;      /* refuse the one that would be this many (0: none) */
 int shim_mallocs = 0;            /* allocations asked for */
 int shim_refuse_malloc = 0;      /* refuse the one that would be this many (0: none) */
+int shim_pinned = 0;             /* pinned allocations held */
 size_t shim_watch_bytes = 0;     /* hipMemsetAsync of this size: */
 void *shim_cleared = NULL;       /* the memory it last cleared */
 
@@ -36,6 +37,20 @@ int hipMalloc(void **p, size_t bytes) {
     if (!real) real = (int (*)(void **, size_t))next_of("hipMalloc");
     if (++shim_mallocs == shim_refuse_malloc) return 2; /* hipErrorOutOfMemory */
     return real(p, bytes);
+}
+
+int hipHostMalloc(void **p, size_t bytes, unsigned flags) {
+    static int (*real)(void **, size_t, unsigned) = NULL;
+    if (!real) real = (int (*)(void **, size_t, unsigned))next_of("hipHostMalloc");
+    ++shim_pinned;
+    return real(p, bytes, flags);
+}
+
+int hipHostFree(void *p) {
+    static int (*real)(void *) = NULL;
+    if (!real) real = (int (*)(void *))next_of("hipHostFree");
+    --shim_pinned;
+    return real(p);
 }
 
 int hipMemsetAsync(void *p, int value, size_t bytes, void *stream) {
