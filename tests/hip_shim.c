@@ -8,6 +8,8 @@
 typedef struct { unsigned x, y, z; } dim3_t;
 
 int shim_cooperative = 0;        /* cooperative launches asked for */
+int shim_no_launch = 0;          /* count them only */
+int shim_strict = 0;             /* a refusal of the runtime's own stands */
 int shim_refuse_launch = 0;      /* refuse the one that would be this many (0: none) */
 int shim_mallocs = 0;            /* allocations asked for */
 int shim_refuse_malloc = 0;      /* refuse the one that would be this many (0: none) */
@@ -29,7 +31,16 @@ int hipLaunchCooperativeKernel(const void *f, dim3_t grid, dim3_t block, void **
     static int (*real)(const void *, dim3_t, dim3_t, void **, unsigned, void *) = NULL;
     if (!real) real = (int (*)(const void *, dim3_t, dim3_t, void **, unsigned, void *))next_of("hipLaunchCooperativeKernel");
     if (++shim_cooperative == shim_refuse_launch) return 720; /* hipErrorCooperativeLaunchTooLarge */
-    return real(f, grid, block, args, lds, stream);
+    if (shim_no_launch) return 0;
+    int e = real(f, grid, block, args, lds, stream);
+    if (e && !shim_strict) { /* one process at a time may launch cooperatively: the few workgroups of a small model fit all the same */
+        int (*clear)(void) = (int (*)(void))next_of("hipGetLastError");
+        int (*plain)(const void *, dim3_t, dim3_t, void **, size_t, void *) =
+            (int (*)(const void *, dim3_t, dim3_t, void **, size_t, void *))next_of("hipLaunchKernel");
+        clear();
+        if (grid.x <= 64) e = plain(f, grid, block, args, lds, stream);
+    }
+    return e;
 }
 
 int hipMalloc(void **p, size_t bytes) {

@@ -5,7 +5,8 @@ import pytest
 
 torch = pytest.importorskip("torch")
 
-from shimmed import run  # noqa: E402
+from paper_2509_01827_amd import mct2d  # noqa: E402
+from shimmed import CONFIGS, run  # noqa: E402
 
 pytestmark = pytest.mark.gpu
 
@@ -57,6 +58,28 @@ for name, cfg in CONFIGS().items():
     m.sync()
     print(name, made, "ok", flush=True)
 """
+
+SECOND_PROCESS = """
+word("shim_strict", 1)
+for name, cfg in CONFIGS().items():
+    m, ref = mct2d.from_config(cfg), mct2d.from_config(cfg, tile=1)
+    for n in (40, 600):
+        m.step(n)
+        ref.step(n)
+        m.sync()
+        assert all(np.array_equal(a, b) for a, b in zip(state(m), state(ref))), (name, n)
+    print(name, word("shim_cooperative"), "ok", flush=True)
+"""
+
+
+def test_a_second_process_on_the_device(tmp_path):
+    """The runtime gives cooperative launches to one process at a time."""
+    m = mct2d.from_config(CONFIGS()["grid"])
+    m.step(100)
+    m.sync()
+    run(SECOND_PROCESS, tmp_path)
+    m.step(100)
+    m.sync()
 
 
 @pytest.mark.parametrize("code", [LAUNCHES, ALLOCATIONS], ids=["launches", "allocations"])
