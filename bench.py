@@ -95,13 +95,13 @@ TRI_SOURCES = ("mct2d_resident_mesh.hip", "mct2d_resident_mesh_host.cpp", "mct2d
                "mct2d_tri.h", "mct2d_device.h", "mct2d_impl.h")
 MEASURED_TRAFFIC = {
     # the batched lattice step kernel over the timed window (profiles/k_step_batch256_hbm_traffic.md)
-    "batch256": {"sources": Q4_SOURCES, "sha256": "b92d59fe58c87bbc741d175015493ce330a02686b64536d240f9e307c8e3b9e1",
-                 "tile": 1, "fetch_kib": 286587.1904296875, "write_kib": 411315.05712890625},
+    "batch256": {"sources": Q4_SOURCES, "sha256": "c4ec3a151c90c29dce1a0f59aaf870bd44f40385e23001fdcf756b205961c649",
+                 "tile": 1, "fetch_kib": 286587.32421875, "write_kib": 411076.5654296875},
     # the resident mesh step, per step of a launch of 512 (profiles/k_mesh_resident.md)
-    "tri320k": {"sources": TRI_SOURCES, "sha256": "b9d3444662e9d50705ce4e2a1fbf8539fc8b1f06cb735cc0f674cfa44ad06278",
-                "tile": 5, "fetch_kib": 1133.5, "write_kib": 1160.1},
-    "quad160k": {"sources": TRI_SOURCES, "sha256": "b9d3444662e9d50705ce4e2a1fbf8539fc8b1f06cb735cc0f674cfa44ad06278",
-                 "tile": 5, "fetch_kib": 1376.5, "write_kib": 1363.8},
+    "tri320k": {"sources": TRI_SOURCES, "sha256": "77363b6098810df288a11f7907e3580fcc48eb2d5fc9f7c86a2002ce62e7d938",
+                "tile": 5, "fetch_kib": 1134.2, "write_kib": 1154.0},
+    "quad160k": {"sources": TRI_SOURCES, "sha256": "77363b6098810df288a11f7907e3580fcc48eb2d5fc9f7c86a2002ce62e7d938",
+                 "tile": 5, "fetch_kib": 1361.4, "write_kib": 1352.2},
 }
 FETCH_SCALE, WRITE_SCALE = 262144.0 / 131086.604, 262144.0 / 262144.0
 
