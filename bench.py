@@ -11,12 +11,13 @@ the multi-tip pick and split.
 
 Timed region: the state is advanced untimed from t = 0 to step --start
 (default 2500, mid-run: cracks growing, candidates live), then --warmup
-untimed steps, then exactly --steps steps (captured graphs) bracketed by
-device synchronisation and HIP events on the model's stream; inputs
-resident in HBM.  The roofline divides the algorithmic bytes of one step by
-that window's time per step (the step kernel plus the per-step pick commit
-of a batch), so it is a lower bound of the step kernel's own rate.  As a
-cross-check the step kernel alone is then timed with HIP events around each
+untimed steps, then exactly --steps steps (captured graphs, or on one grid
+or mesh the resident step's launches of up to 512 steps) bracketed by device
+synchronisation and HIP events on the model's stream; inputs resident in HBM.
+The roofline divides the algorithmic bytes of one step by that window's time
+per step (the step kernel plus the per-step pick commit of a batch), so it is
+a lower bound of the step kernel's own rate; the resident step moves far
+fewer bytes than that.  As a cross-check the per-step kernel alone is then timed with HIP events around each
 launch (mct_profile_step, direct launches) over the next steps.  Prints one
 JSON line.
 
@@ -96,12 +97,12 @@ TRI_SOURCES = ("mct2d_resident_mesh.hip", "mct2d_resident_mesh_host.cpp", "mct2d
 MEASURED_TRAFFIC = {
     # the batched lattice step kernel over the timed window (profiles/k_step_batch256_hbm_traffic.md)
     "batch256": {"sources": Q4_SOURCES, "sha256": "c4ec3a151c90c29dce1a0f59aaf870bd44f40385e23001fdcf756b205961c649",
-                 "tile": 1, "fetch_kib": 286587.32421875, "write_kib": 411076.5654296875},
+                 "tile": 1, "resident": False, "fetch_kib": 286587.32421875, "write_kib": 411076.5654296875},
     # the resident mesh step, per step of a launch of 512 (profiles/k_mesh_resident.md)
     "tri320k": {"sources": TRI_SOURCES, "sha256": "77363b6098810df288a11f7907e3580fcc48eb2d5fc9f7c86a2002ce62e7d938",
-                "tile": 5, "fetch_kib": 1134.2, "write_kib": 1154.0},
+                "tile": 5, "resident": True, "fetch_kib": 1134.2, "write_kib": 1154.0},
     "quad160k": {"sources": TRI_SOURCES, "sha256": "77363b6098810df288a11f7907e3580fcc48eb2d5fc9f7c86a2002ce62e7d938",
-                 "tile": 5, "fetch_kib": 1361.4, "write_kib": 1352.2},
+                 "tile": 5, "resident": True, "fetch_kib": 1361.4, "write_kib": 1352.2},
 }
 FETCH_SCALE, WRITE_SCALE = 262144.0 / 131086.604, 262144.0 / 262144.0
 
@@ -122,10 +123,12 @@ def kernel_sha256(sources) -> str:
     return h.hexdigest()
 
 
-def measured_traffic(workload: str, tile: int):
+def measured_traffic(workload: str, tile: int, resident: bool | None = None):
+    """Measured HBM bytes per step, or None: another tile or (where given)
+    another kind of launch than it was taken on, or changed kernel sources."""
     rec = MEASURED_TRAFFIC.get(workload)
     if rec is None or rec["fetch_kib"] is None or rec["tile"] != tile or \
-            kernel_sha256(rec["sources"]) != rec["sha256"]:
+            resident not in (None, rec["resident"]) or kernel_sha256(rec["sources"]) != rec["sha256"]:
         return None
     return 1024.0 * (rec["fetch_kib"] * FETCH_SCALE + rec["write_kib"] * WRITE_SCALE)
 
@@ -351,6 +354,7 @@ def main():
     lattice = structured and m.lattice()
     gpu_ms, wall, splits = timed_window(m, stream, start, args.warmup, args.steps, nspec)
     launch = m.launch()
+    resident = 0 < m.resident() <= args.steps
     logs = []
     if nspec > 1 or screen:
         for s in range(nspec):
@@ -373,10 +377,12 @@ def main():
     value = ne * args.steps / (gpu_ms * 1e-3)
     bps = bytes_per_step(cfgs, args.precision, lattice)
     # the dominant kernel's launch duration, from the timed window: the time
-    # per step (step kernel + the batch's pick commit, launch gaps included)
+    # per step (step kernel + the batch's pick commit, launch gaps included; a
+    # resident launch: its time divided by its steps)
     kern_us = ms_per_step * 1e3
     achieved = bps / (kern_us * 1e-6) / 1e9
-    graph_ran = not args.no_graph and not screen
+    kernel = ("k_resident" if structured else "k_mesh_resident") if resident else "k_step" if structured else "step"
+    graph_ran = not args.no_graph and not screen and not resident
     out = {
         "metric": "element-updates/s",
         "value": value,
@@ -393,18 +399,24 @@ def main():
         "config": {"workload": WORKLOADS[args.workload], "name": args.workload, "specimens": nspec, "elements": ne,
                    "start_step": start, "window": [start + args.warmup, start + args.warmup + args.steps],
                    "tile": launch["tile"], "order": launch["order"], "workgroups": launch["workgroups"],
-                   "graph": graph_ran, "lattice": lattice, "smoothing": args.smoothing,
+                   "graph": graph_ran, "resident": resident, "lattice": lattice, "smoothing": args.smoothing,
                    "front_radius": args.front_radius, "precision": args.precision, "autotuned": tune is not None},
         "wall_s": wall,
         "splits_in_window": splits,
         "dissipated_J_per_m": ud,
         "roofline": {"bound": "hbm", "achieved": achieved, "peak": HBM_PEAK_GBS, "unit": "GB/s",
-                     "frac": achieved / HBM_PEAK_GBS, "traffic": measured_traffic(args.workload, launch["tile"]),
-                     "bytes_per_launch": bps, "kernel": "k_step" if structured else "step",
+                     "frac": achieved / HBM_PEAK_GBS,
+                     "traffic": measured_traffic(args.workload, launch["tile"], resident),
+                     "bytes_per_launch": bps, "kernel": kernel,
                      "kernel_us": kern_us, "kernel_us_from": "timed window, per step"},
     }
+    if resident:
+        out["roofline"]["note"] = ("bytes_per_launch and achieved are the algorithmic bytes of one step over its time; "
+                                   "the resident step keeps the state on the chip, and its launches of up to 512 "
+                                   "steps move `traffic` bytes a step (null: not measured)")
     if kt:
-        out["kernel_timing"] = {"steps": args.profile_steps, "after_step": start + args.warmup + args.steps,
+        out["kernel_timing"] = {"kernel": "k_step, one launch per step", "steps": args.profile_steps,
+                                "after_step": start + args.warmup + args.steps,
                                 "step_kernel_us": kt["step_us"], "pick_commit_us": kt["commit_us"]}
     m.close()
     if screen:

@@ -483,10 +483,17 @@ int mct_get_near_log(mct_ctx *ctx, int64_t cap, int32_t *step, int32_t *elem, ui
  * and keeps the fastest choice.  On an unstructured mesh the choices are
  * the step kernels of mct_set_launch (1 the element plus node kernels,
  * 2/3/4 the fused kernel on 64/128/256-node patches, 5 on patches of the
- * size it finds).  Outputs (any may be NULL): the chosen tile (as
- * mct_get_launch reports it), order and its time per step in
+ * size it finds).  Where the automatic choice takes launches of many steps
+ * (mct_set_launch) that is a choice too, timed over at least 64 steps; when it
+ * is kept, the launch choice stays automatic and the tile returned is that of
+ * the per-step kernels behind it.  Outputs (any may be NULL): the chosen tile
+ * (as mct_get_launch reports it), order and its time per step in
  * microseconds. */
 int mct_autotune(mct_ctx *ctx, int trial_steps, int *tile, int *order, double *us_per_step);
+
+/* Fewest steps of an mct_step request that the launch of many steps takes (see
+ * mct_set_launch); 0: none does, every request takes the per-step kernels. */
+int mct_get_resident(mct_ctx *ctx, int64_t *min_steps);
 
 /* Launch shape in use: tile index, unit order, workgroups per step (on a
  * unstructured mesh: the step kernels in use, 1 split, 2..4 fused on

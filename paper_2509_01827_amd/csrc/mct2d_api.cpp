@@ -2362,6 +2362,15 @@ int mct_autotune(mct_ctx *c, int trial_steps, int *tile_out, int *order_out, dou
     return MCT_OK;
 }
 
+int mct_get_resident(mct_ctx *c, int64_t *min_steps) {
+    if (!c || !min_steps) return MCT_EINVAL;
+    if (c->tri)
+        *min_steps = c->tri->use_graph && c->tri->res.threads ? mct::tri::kMeshResidentMinSteps : 0;
+    else
+        *min_steps = c->use_graph && c->res.threads && !c->screen_on ? resident_min_steps(c->res) : 0;
+    return MCT_OK;
+}
+
 int mct_get_launch(mct_ctx *c, int *tile, int *order, int64_t *workgroups) {
     if (!c) return MCT_EINVAL;
     if (c->tri) {

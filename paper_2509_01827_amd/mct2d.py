@@ -54,6 +54,7 @@ EXPORTS = [
     "mct_set_load_curve", "mct_set_mesh_tri", "mct_set_mesh_q4", "mct_set_front_pick",
     "mct_set_smoothing", "mct_bind_device_buffers", "mct_set_lattice", "mct_get_lattice",
     "mct_set_near_log", "mct_get_near_log", "mct_profile_step", "mct_get_tips_noalloc", "mct_get_sizes",
+    "mct_get_resident",
 ]
 LATTICE_AUTO = 0
 LATTICE_GENERAL = 1
@@ -115,6 +116,7 @@ def load() -> C.CDLL:
     L.mct_step.argtypes = [P, C.c_int64]
     L.mct_sync.argtypes = [P]
     L.mct_get_info.argtypes = [P, C.POINTER(Info)]
+    L.mct_get_resident.argtypes = [P, C.POINTER(C.c_int64)]
     L.mct_get_sizes.argtypes = [P, C.POINTER(C.c_int64)]
     L.mct_get_crack_set.argtypes = [P, C.c_int64, P, P, P, P, P, C.POINTER(C.c_int64)]
     L.mct_get_tips.argtypes = [P, C.c_int64, P, P, C.POINTER(C.c_int64)]
@@ -368,6 +370,12 @@ class Model:
         t, o, w = C.c_int(0), C.c_int(0), C.c_int64(0)
         self._check(self._L.mct_get_launch(self._h, C.byref(t), C.byref(o), C.byref(w)), "get_launch")
         return dict(tile=t.value, order=o.value, workgroups=w.value)
+
+    def resident(self):
+        """Fewest steps of a request that the launch of many steps takes (0: none)."""
+        n = C.c_int64(0)
+        self._check(self._L.mct_get_resident(self._h, C.byref(n)), "get_resident")
+        return n.value
 
     def finalize(self):
         self._check(self._L.mct_finalize(self._h), "finalize")

@@ -45,3 +45,25 @@ for cfg, least in (((20, 16), 6), ((74, 89), 6), ((75, 89), 4), (tri, 10)):
 @pytest.mark.parametrize("code", [SIZES, STEPS], ids=["sizes", "steps"])
 def test_routes(code, tmp_path):
     run(code, tmp_path)
+
+
+def test_the_route_is_reported(tmp_path):
+    """mct_get_resident: the fewest steps as above, 0 with a tile shape, without graphs, for a batch, screened."""
+    run("""
+plate = W.plate(75, 89, 0.0075, 0.0089, notch_len=30, name="route")
+for cfg, least in ((W.small_cases()["plate40x40"], 6), (plate, 4), (W.tri_plate(40, 16, 0.1, 0.04), 10)):
+    m = mct2d.from_config(cfg)
+    assert m.resident() == least
+    m.set_launch(1, True)
+    assert m.resident() == 0
+    m.set_launch(0, False)
+    assert m.resident() == 0
+    m.set_launch(0, True)
+    assert m.resident() == least
+m = mct2d.from_config(plate)
+mlp = mct2d.Mlp()
+mlp.set_params(np.zeros(mct2d.N_PARAMS, np.float32))
+m.screen_enable(mlp, 0.0, 50)
+assert m.resident() == 0
+assert mct2d.batch_from_configs([plate, plate]).resident() == 0
+""", tmp_path)
