@@ -7,17 +7,20 @@
 // such a step is one chain of latencies, 12 to 14 us on a 40 x 40 plate and on
 // a 400 x 400 one alike.  Here every workgroup owns a tile of nodes for the
 // whole launch: u lives in LDS, v, 1/m, the gradients at the edge midpoints and
-// the smoothing weights in registers, the lists of free-surface candidates and
-// split elements in LDS.  Per step the workgroups exchange the nodes within two
-// of their borders and one candidate slot each, as tagged words
-// (mct2d_exchange.h).
+// the smoothing weights in registers (tiles of 768 elements in binary64 spill 16
+// values per thread, 57 with sub-cells; of 1 024 in binary32 one or two), the
+// lists of free-surface candidates and split elements in LDS.  Per step the
+// workgroups exchange the nodes within two of their borders and one candidate
+// slot each, as tagged words (mct2d_exchange.h).
 //
-// What bounds it: the slowest tile's chain of five barriers (instruction issue:
-// three wavefronts per SIMD and about 500 instructions each on the 400 x 400
-// plate; its candidates and split pieces) and one exchange through the memory
-// side, 0.7 us there and back.  Per step, before -> after: 400 x 400 plate
-// 13.3 -> 6.1 us (binary32 11.9 -> 4.6), 301 x 187 with sub-cells 11.0 -> 5.3,
-// 40 x 40 with cracks running 12.4 -> 4.4.
+// What bounds it: the slowest tile's chain of four barriers (latencies of LDS and
+// dependent arithmetic with three wavefronts per SIMD; its candidates and split
+// pieces) and one exchange through the memory side, 0.7 us there and back.  On the
+// 400 x 400 plate with an element splitting in every step a wavefront issues 392
+// vector instructions per step, a fifth of what the SIMDs could, and waits for 77 %
+// of its cycles.  Per step, before -> after: 400 x 400 plate 13.3 -> 6.1 us
+// (binary32 11.9 -> 4.6), 301 x 187 with sub-cells 11.0 -> 5.3, 40 x 40 with cracks
+// running 12.4 -> 4.4.
 //
 // The arithmetic is k_step's, operation for operation, so results are the
 // same bits: strains at the four edge midpoints, the smoothed stress of an

@@ -8,19 +8,22 @@
 // geometry: 16 us on 320 000 triangles, 20 us on 160 000 quadrilaterals, 10 to
 // 12 us on 54 000 triangles.  Here one workgroup per compute unit owns a patch
 // of up to 768 nodes for the whole launch: u in LDS, v, 1/m, element gradients
-// and smoothing weights in registers.  Patches are runs of a Morton order of
-// the coordinates (any node numbering).  Border nodes and candidate slots
-// travel as tagged words (mct2d_exchange.h).
+// and smoothing weights in registers (768-thread patches of quadrilaterals spill
+// 12 values per thread, 19 with more than eight elements at a node).  Patches are
+// equal counts of nodes from a recursive bisection of the coordinates (any node
+// numbering).  Border nodes and candidate slots travel as tagged words
+// (mct2d_exchange.h).
 //
-// What bounds it: the slowest patch's chain of a step, instruction issue of
-// three wavefronts per SIMD and LDS (per 320 000 triangles: strains 1200
-// cycles, smoothing and forces 4500, candidates 2500, sums 2200, the exchange
-// 2500 to 4000), hence also the strides of the LDS arrays, at which the
-// wavefronts' accesses share no banks.  Per step, before -> after: 320 000
-// triangles 16.2 -> 6.7 us, 160 000 quadrilaterals 21 -> 7.7, 54 000 triangles
-// with cracks running 11 -> 6.0.
+// What bounds it: the slowest patch's chain of a step (barriers, latencies of LDS
+// and dependent arithmetic with three wavefronts per SIMD) and the exchange.  Over
+// the chip vector issue is busy 35 % of the time on 320 000 triangles and 30 % on
+// 160 000 quadrilaterals (460 instructions per wavefront and step); wavefronts wait
+// for 69 and 74 % of their cycles.  The strides of the LDS arrays spread a
+// wavefront's accesses over the banks; conflicts take 8 to 10 % of the cycles.
+// Per step, before -> after: 320 000 triangles 16.2 -> 6.7 us, 160 000
+// quadrilaterals 21 -> 7.7, 54 000 triangles with cracks running 11 -> 6.0.
 //
-// A step, with four barriers (five on quadrilaterals):
+// A step, with three barriers (four on quadrilaterals):
 //   - the pick of the step before acts on the codes; every element of the patch
 //     and of its ring (triangles; on quadrilaterals the ring's shared edges)
 //     stores its strains in LDS;
