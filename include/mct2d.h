@@ -299,9 +299,9 @@ int mct_profile_step(mct_ctx *ctx, int64_t n, double out_us[2]);
 /* Wait for the enqueued work; reports asynchronous device errors, and
  * MCT_ENUMERIC if any displacement or velocity of the current step is not
  * finite.  A launch of many steps whose workgroups did not all answer one
- * another (MCT_EDEVICE here, from mct_checkpoint and from every query that
- * waits for the device) leaves a state of no use; the error stays until
- * mct_restore or mct_finalize. */
+ * another within half a minute leaves a state of no use: MCT_EDEVICE here,
+ * from mct_checkpoint and from every query of the state that waits for the
+ * device, until mct_restore or mct_finalize. */
 int mct_sync(mct_ctx *ctx);
 
 int mct_get_info(mct_ctx *ctx, mct_info *out);
